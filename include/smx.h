@@ -268,7 +268,14 @@ int smx_edm_tiled(const float *d_X, int64_t n, int64_t d, int64_t ldx, int map, 
  * against fl(rc*rc).  Coincident particles give inf/NaN (not checked).
  *   d_X   FP32 [n][ldx], ldx >= 3 (only x, y, z are read).
  *   d_E   FP64 [3]: total, Axilrod-Teller part, Lennard-Jones part.
- *   d_ws  smx_workspace_bytes(2, n, 3, 0, map) bytes.
+ *   d_ws  smx_workspace_bytes(2, n, 3, 0, map) bytes.  That size gives the
+ *         fastest form; any size from 3 * 32768 + 24 n bytes (rounded up to 256) is
+ *         accepted.  From n = 768 (energy alone: 1024) to 2^18 the triplets are
+ *         summed as matrix products on the matrix cores, whose operands (at most
+ *         3 GiB, 40 n^2 bytes) lie in d_ws after that minimum, as many at a time as
+ *         fit; `map` then orders the pair tiles of the 2-simplex, all k of a tile
+ *         being one block's k loop.  Smaller n, smaller workspaces and calls with
+ *         statistics walk the 3-simplex tile by tile.
  *   d_stats nullable, int64[8]: [0..3] triplets lt, [4..7] pairs lt.
  * E = 0 for n < 3 (AT) and n < 2 (LJ). */
 int smx_triplet_energy(const float *d_X, int64_t n, int64_t ldx, const smx_pot *pot, int map,

@@ -193,6 +193,51 @@ static TripWs trip_ws(int64_t n) {
     return w;
 }
 
+// The matrix form of the Axilrod-Teller calls: nearest-neighbour words [n] after
+// the base layout, then the operand panels, 4 bytes (hi and lo) per form, row and
+// column.
+struct AtWs {
+    size_t near, zero_end, ops, total;
+    AtPlan plan;
+};
+constexpr size_t kAtOpsMax = size_t(3) << 30;
+static size_t at_ops_bytes(int64_t n, int nr, int64_t kc) {
+    return size_t(nr) * 4 * size_t((n + 31) / 32 * 32) * size_t((kc + 31) / 32 * 32);
+}
+// The plan that fits `bytes` of workspace: all columns of as many forms as fit,
+// else one form and fewer columns.
+static AtWs at_ws(int64_t n, size_t bytes) {
+    AtWs w{};
+    w.near = trip_ws(n).total;
+    w.zero_end = w.near + align256(size_t(n) * 4);
+    w.ops = w.zero_end + 256;  // room to align the panels
+    if (bytes <= w.ops) return w;
+    size_t room = bytes - w.ops;
+    if (room > kAtOpsMax) room = kAtOpsMax;
+    w.plan.kc = n;
+    for (int nr : {10, 5, 2, 1})
+        if (at_ops_bytes(n, nr, n) <= room) {
+            w.plan.nr = nr;
+            break;
+        }
+    if (w.plan.nr == 0) {
+        w.plan.kc = int64_t(room / (4 * size_t((n + 31) / 32 * 32))) / 256 * 256;
+        w.plan.nr = w.plan.kc >= 2048 ? 1 : 0;
+    }
+    w.total = w.ops + at_ops_bytes(n, w.plan.nr, w.plan.kc);
+    return w;
+}
+// The matrix form does the triplets of n particles as n^3 products on the matrix
+// cores against n^3 / 6 triplets of about 25 vector instructions: gradient, ms,
+// matrix / loop: n = 500 0.051 / 0.036, 1000 0.090 / 0.179, 2051 0.37 / 1.94, 8192
+// 13.9 / 52.7; energy: 500 0.040 / 0.018, 1000 0.067 / 0.068, 2051 0.18 / 0.50, 8192
+// 6.0 / 21.  Below the line its launches and the depth of its k loop cost more
+// than the loop's arithmetic.  Past 2^18 fewer than 2048 columns of one form fit
+// kAtOpsMax, and each chunk of columns pays the pairs' epilogue again.
+static bool at_matrix_form(int64_t n, bool grad) { return n >= (grad ? 768 : 1024) && n <= (int64_t(1) << 18); }
+// Edge of its pair tiles: see AtTile.
+static int at_pair_tile(int64_t n, bool grad) { return n >= (grad ? 4096 : 8192) ? 256 : 128; }
+
 struct QuadWs {
     size_t cslots, sslots, words, total;
     int64_t nb, npad;
@@ -250,7 +295,7 @@ size_t smx_workspace_bytes(int op, int64_t n, int64_t d, int prec, int map) {
         if (d < 1 || prec < 0 || prec > 2) return 0;
         return edm_ws(n, d, prec).total;
     }
-    if (op == 2) return trip_ws(n).total;
+    if (op == 2) return at_matrix_form(n, true) ? at_ws(n, ~size_t(0)).total : trip_ws(n).total;
     if (op == 3) return quad_ws(n).total;
     return 0;
 }
@@ -493,10 +538,23 @@ static int triplet_run(int mode, const float *d_X, int64_t n, int64_t ldx, const
     double *G64 = reinterpret_cast<double *>(ws + w.g64);
     hipStream_t s = S(stream);
     // zero energy slots, statistics slots and the FP64 gradient in one fill
-    const size_t zero_words = (mode == 0 ? (d_stats ? w.g64 : w.at_stats) : w.total) / 8;
+    const AtWs aw = do_at && d_stats == nullptr && !static_ws && at_matrix_form(n, mode >= 1) ? at_ws(n, ws_bytes) : AtWs{};
+    MapGeom gp;
+    const int ptile = at_pair_tile(n, mode >= 1);
+    const int64_t nbp = (n + ptile - 1) / ptile;
+    // from above, lambda2 filters up to three ids in four where nbp is no power of
+    // two, in stretches that left XCDs idle (n = 2051: 0.45 against 0.37 ms)
+    const bool matrix = aw.plan.nr != 0 && make_geom(2, nbp, map == MAP_LAMBDA && !pow2(nbp) ? MAP_BELOW : map, gp);
+    const size_t zero_words =
+        (matrix ? aw.zero_end : mode == 0 ? (d_stats ? w.g64 : w.at_stats) : w.total) / 8;
     if ((rc = launch_fill_u64(reinterpret_cast<uint64_t *>(ws), zero_words, s))) return rc;
     const bool grad = mode >= 1;
-    if (do_at && (rc = launch_triplet(g3, d_X, n, ldx, float(pot->nu), grad, G64, eslots, at_st, s))) return rc;
+    if (matrix) {
+        const uintptr_t ops = (reinterpret_cast<uintptr_t>(ws) + aw.ops - 256 + 255) & ~uintptr_t(255);
+        if ((rc = launch_triplet_mfma(gp, ptile, aw.plan, d_X, n, ldx, float(pot->nu), grad, G64, eslots,
+                                      reinterpret_cast<unsigned *>(ws + aw.near), reinterpret_cast<void *>(ops), s)))
+            return rc;
+    } else if (do_at && (rc = launch_triplet(g3, d_X, n, ldx, float(pot->nu), grad, G64, eslots, at_st, s))) return rc;
     if (do_lj && (rc = launch_lj(g2, d_X, n, ldx, float(pot->lj_eps), float(pot->lj_sigma),
                                  float(pot->lj_rc * pot->lj_rc), G64, eslots, lj_st, s)))
         return rc;
@@ -608,7 +666,7 @@ int smx_check_flags(uint32_t *flags, int clear) {
     const bool c = clear != 0;
     const unsigned parts[] = {check_flags_edm(c),  check_flags_gram(c),    check_flags_map(c),
                               check_flags_quad(c), check_flags_tripack(c), check_flags_triplet(c),
-                              check_flags_life(c)};
+                              check_flags_life(c), check_flags_triplet_mfma(c)};
     unsigned v = 0;
     for (unsigned p : parts) {
         if (p == ~0u) return fail(SMX_EHIP, "reading the device check flags failed");

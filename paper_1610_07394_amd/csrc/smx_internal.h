@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "smx.h"
+#include "smx_at_forms.h"
 #include "smx_maps.h"
 
 namespace smx {
@@ -39,6 +40,7 @@ unsigned check_flags_quad(bool clear);
 unsigned check_flags_tripack(bool clear);
 unsigned check_flags_triplet(bool clear);
 unsigned check_flags_life(bool clear);
+unsigned check_flags_triplet_mfma(bool clear);
 
 // Kernel ids for the timing facility (match smx_profile_read).
 enum KernelId {
@@ -152,6 +154,14 @@ constexpr int kTripTile = 32;    // Axilrod-Teller: 32^3 triplets per block
 constexpr int kLjTile = 64;      // Lennard-Jones: 64 x 64 pairs per block
 int launch_triplet(const MapGeom &g, const float *X, int64_t n, int64_t ldx, float nu, bool grad,
                    double *G64, double *eslots, unsigned long long *sslots, hipStream_t s);
+// Axilrod-Teller in matrix form: kAtForms operand matrices of n x n FP16 pairs,
+// made nr forms and kc columns at a time in caller-given memory.
+struct AtPlan {
+    int nr;      // forms per launch (10, 5, 2 or 1); 0: no plan
+    int64_t kc;  // columns per launch
+};
+int launch_triplet_mfma(const MapGeom &g, int tile, const AtPlan &plan, const float *X, int64_t n, int64_t ldx, float nu,
+                        bool grad, double *G64, double *eslots, unsigned *near, void *ops, hipStream_t s);
 int launch_lj(const MapGeom &g, const float *X, int64_t n, int64_t ldx, float eps, float sigma,
               float rc2, double *G64, double *eslots, unsigned long long *sslots, hipStream_t s);
 int launch_energy_finalize(const double *eslots, double *E, hipStream_t s);

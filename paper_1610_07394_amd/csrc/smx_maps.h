@@ -636,4 +636,14 @@ SMX_HD uint32_t xcd_remap(uint32_t b, uint32_t G) {
     return x * chunk + (x < rem ? x : rem) + s;
 }
 
+// As xcd_remap, but in runs of 2^lg logical blocks dealt to the XCDs in turn:
+// neighbours still share an L2, and a map whose filtered or light blocks come in
+// long stretches loads every XCD alike.  The last G mod 8 * 2^lg blocks keep their
+// places.  A bijection on [0, G).
+SMX_HD uint32_t xcd_deal(uint32_t b, uint32_t G, int lg) {
+    if (b >= (G >> (lg + 3) << (lg + 3))) return b;
+    const uint32_t x = b & 7u, s = b >> 3, run = 1u << lg;
+    return (((s >> lg) << 3 | x) << lg) | (s & (run - 1u));
+}
+
 }  // namespace smx

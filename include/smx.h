@@ -348,7 +348,10 @@ int smx_triplet_packed_tiled(const float *d_X, int64_t n, int64_t ldx, double nu
  * distance fl(fma(dz,dz, fma(dy,dy, dx*dx))), d* = fl(x_j* - x_i*), is below
  * fl(rc*rc).  Two passes over 64-element tiles: contact bit words over the
  * 2-simplex (map `map` with m = 2), then the cliques over the 4-simplex (map
- * `map` with m = 4; LAMBDA is the lambda4 map of smx_simplex_map4).
+ * `map` with m = 4; LAMBDA is the lambda4 map of smx_simplex_map4).  Without
+ * statistics and from n = 256 on, a sparse contact graph is counted from its
+ * contacts instead: for every contact i < j the common neighbours, over the
+ * 2-simplex tiles of pass one (the device decides by the contacts it found).
  *   d_X      FP32 [n][ldx] device, x, y, z in columns 0..2; ldx >= 3.
  *   n        0 <= n <= 16384 (n < 4 gives 0).
  *   rc       contact radius, finite and >= 0.
@@ -356,8 +359,9 @@ int smx_triplet_packed_tiled(const float *d_X, int64_t n, int64_t ldx, double nu
  *   d_count  int64[1] device: the number of 4-cliques (exact).
  *   d_ws     smx_workspace_bytes(3, n, 3, 0, map) bytes of device memory:
  *            count and statistics slots, then the contact words, 64-bit,
- *            column-tile-major: word [Y][64 X + p] holds the contacts of row
- *            64 X + p with columns 64 Y .. 64 Y + 63 (upper tiles X <= Y only).
+ *            column-tile-major or row-major: word [Y][64 X + p] or [64 X + p][Y]
+ *            holds the contacts of row 64 X + p with columns 64 Y .. 64 Y + 63
+ *            (upper tiles X <= Y only).  Scratch.
  *   d_stats  int64[4] or NULL: [0] quadruplets covered (C(n, 4) when every tile
  *            is visited once), [1] 0, [2] mapped 4-simplex blocks, [3] 4-simplex
  *            blocks of the parallel space (logical blocks: the clique pass

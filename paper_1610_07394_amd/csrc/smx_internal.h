@@ -169,8 +169,10 @@ int launch_triplet_packed(const MapGeom &g, const float *X, int64_t n, int64_t l
                           unsigned long long *sslots, bool tiled, hipStream_t s);
 constexpr int kQuadTile = 64;    // 4-point contacts: 64 elements per tile dimension
 int launch_contact_words(const MapGeom &g, const float *X, int64_t n, int64_t ldx, float rc2, uint64_t *W,
-                         int64_t npad, hipStream_t s);
-int launch_quad(const MapGeom &g, const uint64_t *W, int64_t npad, int64_t n, unsigned long long *cslots,
+                         int64_t npad, unsigned long long *cslots, bool rows, hipStream_t s);
+int launch_quad_rows(const MapGeom &g, const uint64_t *R, int64_t n, bool gated, unsigned long long *cslots,
+                     hipStream_t s);
+int launch_quad(const MapGeom &g, const uint64_t *W, int64_t npad, int64_t n, bool gated, unsigned long long *cslots,
                 unsigned long long *sslots, hipStream_t s);
 constexpr int kLifeTile = 64;    // cellular automaton: 64 x 64 cells per tile
 int launch_life(const MapGeom &g, const uint8_t *S, uint8_t *D, int64_t n, unsigned long long *slots,

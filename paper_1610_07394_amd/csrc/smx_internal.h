@@ -166,7 +166,8 @@ int launch_lj(const MapGeom &g, const float *X, int64_t n, int64_t ldx, float ep
               float rc2, double *G64, double *eslots, unsigned long long *sslots, hipStream_t s);
 int launch_energy_finalize(const double *eslots, double *E, hipStream_t s);
 int launch_triplet_packed(const MapGeom &g, const float *X, int64_t n, int64_t ldx, float nu, float *E,
-                          unsigned long long *sslots, bool tiled, hipStream_t s);
+                          unsigned long long *sslots, bool tiled, bool rows, hipStream_t s);
+// (rows: g is the 2-simplex of kTripTile pair tiles, else the 3-simplex of triplet tiles)
 constexpr int kQuadTile = 64;    // 4-point contacts: 64 elements per tile dimension
 int launch_contact_words(const MapGeom &g, const float *X, int64_t n, int64_t ldx, float rc2, uint64_t *W,
                          int64_t npad, unsigned long long *cslots, bool rows, hipStream_t s);

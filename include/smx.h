@@ -97,7 +97,7 @@ typedef enum {
 } smx_map;
 
 typedef enum {
-    SMX_EDM_FP32_DIFF = 0,      /* sum_k (x_ik - x_jk)^2 in FP32 on the vector ALUs */
+    SMX_EDM_FP32_DIFF = 0,      /* sum_k (x_ik - x_jk)^2 to FP32 accuracy */
     SMX_EDM_BF16_GRAM = 1,      /* |x_i|^2 + |x_j|^2 - 2 G_ij, G on BF16 MFMA, FP32 accumulation */
     SMX_EDM_SPLITBF16_GRAM = 2  /* as 1 with G = hi.hi + hi.lo + lo.hi (split BF16) */
 } smx_edm_prec;
@@ -238,9 +238,14 @@ int smx_simplex_count(int m, int64_t n, int rho, int map, int strict, int64_t *d
  *   prec  smx_edm_prec.  Gram variants round X to BF16 with round-to-nearest-even
  *         (hi = bf16(x), lo = bf16(x - hi)), accumulate in FP32, add FP32 norms
  *         |x|^2, clamp the result at 0.
- *   d_ws  smx_workspace_bytes(1, n, d, prec, map) bytes, or NULL when that is 0:
- *         statistics slots and, for the Gram variants, FP32 norms and the BF16
- *         hi (and lo) copies of X, rows padded to a multiple of 32 and columns
+ *         FP32_DIFF runs on the matrix cores from n = 8192 and d = 36 (n = 5120
+ *         from d = 64) on: a centred Gram form of FP16 hi + lo pairs (2^-23) with
+ *         FP32 sums for the pairs it is exact for, the difference form for the
+ *         others (near points, NaN, infinities).
+ *   d_ws  smx_workspace_bytes(1, n, d, prec, map) bytes.  For FP32_DIFF, NULL (or,
+ *         with statistics, 32768 bytes) is accepted too and takes the difference
+ *         form on the vector ALUs.  Holds statistics slots, FP32 norms and scales
+ *         and the 16-bit hi (and lo) copies of X, rows padded to a multiple of 32 and columns
  *         to a multiple of 32, stored in the matrix-core operand order (1 KB
  *         per 32-row x 16-column block).  Its contents are scratch.
  *   d_stats nullable; counts pairs le. */

@@ -234,6 +234,9 @@ def simplex_count(m: int, n: int, rho: int, map="lambda", strict=False, device="
 
 
 # ---------------------------------------------------------------- EDM
+_EDM_WS_ROWS = 5120  # FP32 below this takes no workspace (edm_fp32_matrix in smx_abi.hip)
+
+
 def edm_packed(X: torch.Tensor, map="lambda", prec="fp32", stats=False, out=None, ws=None):
     """Packed upper-triangle squared distances of the rows of X (FP32 [n, d])."""
     if X.dtype != torch.float32 or X.dim() != 2 or X.stride(1) != 1:
@@ -243,9 +246,8 @@ def edm_packed(X: torch.Tensor, map="lambda", prec="fp32", stats=False, out=None
     p = PRECS[prec] if isinstance(prec, str) else int(prec)
     D = out if out is not None else torch.empty(n * (n + 1) // 2, dtype=torch.float32, device=X.device)
     s = torch.zeros(4, dtype=torch.int64, device=X.device) if stats else None
-    need = workspace_bytes(1, n, d, p, map)
-    if ws is None and (p != 0 or stats):
-        ws = _ws(need, X.device)
+    if ws is None and (p != 0 or stats or n >= _EDM_WS_ROWS):
+        ws = _ws(workspace_bytes(1, n, d, p, map), X.device)
     _check(lib().smx_edm_packed(_dev(X, "X"), n, d, ldx, _map(map), p, _ptr(D), _ptr(ws),
                                 0 if ws is None else ws.numel(), _ptr(s), _stream()))
     return (D, s) if stats else D
@@ -269,7 +271,7 @@ def edm_tiled(X: torch.Tensor, map="lambda", prec="fp32", stats=False, out=None,
     if D.dtype != torch.float32 or D.numel() < edm_tiled_len(n) or not D.is_contiguous():
         raise ValueError("out must be a contiguous FP32 tensor of edm_tiled_len(n) elements")
     s = torch.zeros(4, dtype=torch.int64, device=X.device) if stats else None
-    if ws is None and (p != 0 or stats):
+    if ws is None and (p != 0 or stats or n >= _EDM_WS_ROWS):
         ws = _ws(workspace_bytes(1, n, d, p, map), X.device)
     _check(lib().smx_edm_tiled(_dev(X, "X"), n, d, ldx, _map(map), p, _ptr(D), _ptr(ws),
                                0 if ws is None else ws.numel(), _ptr(s), _stream()))

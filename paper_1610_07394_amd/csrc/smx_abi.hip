@@ -160,25 +160,35 @@ static inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 // Workspace layouts.
 struct EdmWs {
-    size_t slots, hi, lo, norms, total;
+    size_t slots, hi, lo, norms, inv, near, total;
 };
 static EdmWs edm_ws(int64_t n, int64_t d, int prec) {
     EdmWs w{};
     w.slots = 0;
     size_t off = kSlotBytes;
-    if (prec != SMX_EDM_FP32_DIFF) {
-        const int64_t dpad = (d + kGramK - 1) / kGramK * kGramK;
-        const int64_t npad = gram_rows(n);
-        w.hi = off;
-        off = align256(off + size_t(npad) * size_t(dpad) * 2);
-        w.lo = off;
-        if (prec == SMX_EDM_SPLITBF16_GRAM) off = align256(off + size_t(npad) * size_t(dpad) * 2);
-        w.norms = off;
+    const int64_t dpad = (d + kGramK - 1) / kGramK * kGramK;
+    const int64_t npad = gram_rows(n);
+    w.hi = off;
+    off = align256(off + size_t(npad) * size_t(dpad) * 2);
+    w.lo = off;
+    if (prec != SMX_EDM_BF16_GRAM) off = align256(off + size_t(npad) * size_t(dpad) * 2);
+    w.norms = off;
+    off = align256(off + size_t(n) * 4);
+    if (prec == SMX_EDM_FP32_DIFF) {
+        w.inv = off;
         off = align256(off + size_t(n) * 4);
+        w.near = off;
+        off = align256(off + 64 * 4);
     }
     w.total = off;
     return w;
 }
+// FP32 on the matrix cores: where the products outweigh the preparation and the
+// wider tiles (a caller may skip the workspace below the first n).  ms, matrix / difference form: n = 4096 d = 64 0.042 / 0.034, n = 6000 d
+// = 32 0.061 / 0.054, d = 64 0.062 / 0.094, n = 9001 d = 37 0.094 / 0.199, n = 65536 d =
+// 64 2.6 / 6.3; with every second pair near (difference form in either) n = 9001 d =
+// 37 0.16 / 0.21, n = 65536 d = 64 6.3 / 6.2.  d <= 8192: the centre lies in LDS.
+static bool edm_fp32_matrix(int64_t n, int64_t d) { return n >= (d >= 64 ? 5120 : 8192) && d >= 36 && d <= 8192; }
 
 struct TripWs {
     size_t eslots, at_stats, lj_stats, g64, total;
@@ -300,7 +310,7 @@ size_t smx_workspace_bytes(int op, int64_t n, int64_t d, int prec, int map) {
     if (op == 0) return kSlotBytes;
     if (op == 1) {
         if (d < 1 || prec < 0 || prec > 2) return 0;
-        return edm_ws(n, d, prec).total;
+        return prec == SMX_EDM_FP32_DIFF && !edm_fp32_matrix(n, d) ? kSlotBytes : edm_ws(n, d, prec).total;
     }
     if (op == 2) return at_matrix_form(n, true) ? at_ws(n, ~size_t(0)).total : trip_ws(n).total;
     if (op == 3) return quad_ws(n).total;
@@ -462,25 +472,36 @@ static int edm_run(bool tiled, const float *d_X, int64_t n, int64_t d, int64_t l
     if (n == 0) return SMX_OK;
     if (d_X == nullptr || d_D == nullptr) return fail(SMX_EINVAL, "X and D must not be NULL");
     const EdmWs w = edm_ws(n, d, prec);
-    const bool need_ws = prec != SMX_EDM_FP32_DIFF || d_stats != nullptr;
-    if (need_ws && (d_ws == nullptr || ws_bytes < w.total))
-        return fail(SMX_EINVAL, "workspace of %zu bytes required (got %zu)", w.total, ws_bytes);
-    const int tile = tiled ? kEdmTiledTile : prec == SMX_EDM_FP32_DIFF ? edm_diff_tile(n) : gram_tile(n);
+    const bool fp32 = prec == SMX_EDM_FP32_DIFF;
+    const size_t need = fp32 ? (d_stats != nullptr ? kSlotBytes : 0) : w.total;
+    if (need > 0 && (d_ws == nullptr || ws_bytes < need))
+        return fail(SMX_EINVAL, "workspace of %zu bytes required (got %zu)", need, ws_bytes);
+    const bool matrix = fp32 && edm_fp32_matrix(n, d) && d_ws != nullptr && ws_bytes >= w.total;
+    const int tile = tiled ? kEdmTiledTile : fp32 && !matrix ? edm_diff_tile(n) : gram_tile(n);
     MapGeom g;
     if (!make_geom(2, (n + tile - 1) / tile, map, g)) return g_status;
+    // where nb is no power of two, lambda2 from above filters up to three ids in four, in
+    // stretches that leave XCDs idle; from below lists the same tiles (statistics keep
+    // the map's own count of blocks)
+    if (matrix && map == MAP_LAMBDA && d_stats == nullptr && !pow2(g.nb) && !make_geom(2, g.nb, MAP_BELOW, g)) return g_status;
     char *ws = reinterpret_cast<char *>(d_ws);
     unsigned long long *slots = d_stats ? reinterpret_cast<unsigned long long *>(ws + w.slots) : nullptr;
     int rc;
     if (slots && (rc = launch_fill_u64(reinterpret_cast<uint64_t *>(slots), kSlotBytes / 8, S(stream))))
         return rc;
-    if (prec == SMX_EDM_FP32_DIFF) {
+    const int64_t dpad = (d + kGramK - 1) / kGramK * kGramK;
+    uint16_t *hi = reinterpret_cast<uint16_t *>(ws + w.hi);
+    uint16_t *lo = reinterpret_cast<uint16_t *>(ws + w.lo);
+    float *norms = reinterpret_cast<float *>(ws + w.norms);
+    if (matrix) {
+        float *inv = reinterpret_cast<float *>(ws + w.inv);
+        unsigned *near = reinterpret_cast<unsigned *>(ws + w.near);
+        rc = launch_edm_prep(d_X, n, d, ldx, dpad, near, hi, lo, norms, inv, S(stream));
+        if (rc == SMX_OK) rc = launch_edm_matrix(g, hi, lo, norms, inv, near, n, dpad, d_X, d, ldx, d_D, slots, tiled, S(stream));
+    } else if (fp32) {
         rc = launch_edm_diff(g, tile, d_X, n, d, ldx, d_D, slots, tiled, S(stream));
     } else {
         const bool split = prec == SMX_EDM_SPLITBF16_GRAM;
-        const int64_t dpad = (d + kGramK - 1) / kGramK * kGramK;
-        uint16_t *hi = reinterpret_cast<uint16_t *>(ws + w.hi);
-        uint16_t *lo = reinterpret_cast<uint16_t *>(ws + w.lo);
-        float *norms = reinterpret_cast<float *>(ws + w.norms);
         rc = launch_gram_prep(d_X, n, d, ldx, dpad, hi, lo, norms, split, S(stream));
         if (rc == SMX_OK) rc = launch_edm_gram(g, tile, hi, lo, norms, n, dpad, split, d_D, slots, tiled, S(stream));
     }

@@ -13,7 +13,10 @@
 // of 16 BF16 through a 32 KB ring of LDS slots filled directly from global
 // memory in MFMA fragment order (see the staging notes below), so the loads
 // of the next steps are in flight while the matrix cores run the current one.
+#include <type_traits>
+
 #include "smx_device.h"
+#include "smx_edm_tile.h"
 #include "smx_internal.h"
 
 namespace smx {
@@ -316,6 +319,7 @@ __global__ __launch_bounds__(kGramThreads, 4) void edm_gram_kernel(MapGeom g, co
     static_assert(T == 128 && kGramThreads == 256, "the store loop assumes 4 waves and 128-wide tile rows");
     float *St = reinterpret_cast<float *>(Lb);  // [2 * 32 rows][T], the rows of one pass
     const bool interior = !diag && I0 + T <= n && J0 + T <= n;
+    __syncthreads();  // nA and nB are other threads' work (the k loop's barriers order no LDS writes)
     float nb[MT];
 #pragma unroll
     for (int c = 0; c < MT; ++c) nb[c] = nB[wn * WT + c * 32 + (lane & 31)];
@@ -423,6 +427,527 @@ int launch_edm_gram(const MapGeom &g, int tile, const uint16_t *hi, const uint16
     });
     prof_end(K_EDM_GRAM, s);
     return check_launch("edm_packed (gram)");
+}
+
+
+// ---------------------------------------------------------------- FP32, matrix form
+// The difference form costs two vector operations per element and dimension (n =
+// 65536, d = 64: 6.3 ms, of which the stores need 2).  This form keeps its FP32
+// accuracy on the matrix cores.  Coordinates less a common centre are held as FP16
+// pairs hi + lo (2^-23, each row scaled by a power of two); G = hi hi^T + hi lo^T + lo
+// hi^T in exact products and FP32 sums; D = (|x_i|^2 - 2 G_ij) + |x_j|^2 with norms
+// summed in FP64.  A pair's value stands where it is as exact as the difference
+// form's: D >= 5/16 (|x_i|^2 + |x_j|^2) and finite.  Any other pair (near points, NaN,
+// infinities, overflow) is summed as the difference form does, in its order, from the
+// FP32 input: one thread a pair where a pass of 64 rows has few, else all of the
+// pass's, rows in registers.  Its value does not depend on the tile that holds it.
+// Where more than one of 1024 sampled pairs in 50 is such a pair, every block takes the
+// difference form's tile.  2-norm error, d = 37 / 64 / 130: 4.5 / 4.8 / 5e-8 against
+// 9.4 / 12 / 17e-8.
+//
+// Stores.  Packed rows (i, .) start at any 4-byte offset.  A block's row i is shifted
+// left by s_i < 32 columns to where its piece starts a 128-byte line: rows of tile (X,
+// Y) hold the columns J0 - s_i .. J0 + 127 - s_i (the last tile's to n, the first
+// tile's from i), the block computes one 32-column block more on the left (5 / 4 of
+// the products), and all stores but those at the ends of a packed row are whole
+// lines, streaming.
+//
+// n = 65536, d = 64: 6.3 -> 2.6 ms (3.3 TB/s of stores); 20000, 100: 2.4 -> 0.38; 9001,
+// 37: 0.20 -> 0.09.
+constexpr int kLineCols = 160;           // 32 + 128 columns of a tile row
+constexpr int kLineLd = kLineCols + 4;   // LDS row: shifted by s_i mod 4 floats
+constexpr int kLineList = 128;
+// share of |x_i|^2 + |x_j|^2 from which a pair's Gram value is kept
+constexpr float kEdmNear = 0.3125f;
+// blocks of the preparation that sample 16 pairs each
+constexpr int kEdmSampleBlocks = 64, kEdmSamples = kEdmSampleBlocks * 16;
+
+typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ f32x16_t line_mfma(bf16x8_t a, bf16x8_t b, f32x16_t c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0,
+                                                  0, 0);
+}
+
+// sum_k (x_ik - x_jk)^2 in the difference form's order
+__device__ __forceinline__ float edm_pair(const float *__restrict__ xi, const float *__restrict__ xj, int64_t d) {
+    float acc = 0.f;
+#pragma unroll 8
+    for (int64_t k = 0; k < d; ++k) {
+        const float u = xi[k] - xj[k];
+        acc = __builtin_fmaf(u, u, acc);
+    }
+    return acc;
+}
+
+// Names a fragment register, so that no use of it moves above the wait before this.
+__device__ __forceinline__ void asm_use(bf16x8_t &v) { asm volatile("" : "+v"(v)); }
+
+// Keeps memory accesses in program order here.
+__device__ __forceinline__ void mem_order() { asm volatile("" ::: "memory"); }
+__device__ __forceinline__ void line_load(const uint4 *src, uint4 *lds) {
+    __builtin_amdgcn_global_load_lds(src, lds, 16, 0, 0);
+}
+
+
+// One stage: a 16-wide k block of both panels, [part][row panel 4, column panel 4 + EX]
+// 1 KB blocks, five loads a wave (two waves' last repeats their one before).
+template <int NP, int CB>
+__device__ __forceinline__ void line_issue(uint4 *buf, const uint4 *__restrict__ hi, const uint4 *__restrict__ lo,
+                                           int64_t ra, int64_t rc, int64_t rbmax, int64_t KB, int64_t kb, int wave,
+                                           int lane) {
+    constexpr int PER = 4 + CB, TOT = NP * PER, LPW = (TOT + 3) / 4;
+#pragma unroll
+    for (int t = 0; t < LPW; ++t) {
+        int g = wave + 4 * t;
+        g = g < TOT ? g : g - 4;
+        const int part = g / PER, b = g % PER;
+        int64_t rb = b < 4 ? ra + b : rc + (b - 4);
+        rb = rb < 0 ? 0 : rb < rbmax ? rb : rbmax;  // blocks outside the operand: never used
+        line_load((part ? lo : hi) + (rb * KB + kb) * 64 + lane, buf + g * 64);
+    }
+}
+
+// The pairs of one pass (64 rows x 160 columns in LDS) that are marked -1, summed as
+// differences: thread (t & 31, t >> 5) takes 5 columns by 4 rows at a time.
+__device__ __forceinline__ void edm_pass_diff(float *St, const float4 *rowinfo, const float *__restrict__ X, int64_t n, int64_t d,
+                                           int64_t ldx, int64_t I0, int64_t J0, int m, int c0, int t) {
+    const int tx = t & 31, ty = t >> 5;
+#pragma unroll 1
+    for (int h = 0; h < 64; h += 32) {
+        float acc[4][5];
+        const float *xr[4], *xc[5];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int rr = h + ty + 8 * r;
+            const int64_t i = I0 + (rr >> 5) * 64 + m * 32 + (rr & 31);
+            xr[r] = X + (i < n ? i : n - 1) * ldx;
+#pragma unroll
+            for (int c = 0; c < 5; ++c) acc[r][c] = 0.f;
+        }
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+            const int64_t j = J0 - 32 + tx + 32 * c;
+            xc[c] = X + (j < 0 ? 0 : j < n ? j : n - 1) * ldx;
+        }
+#pragma unroll 2
+        for (int64_t k = 0; k < d; ++k) {
+            float a[4], b[5];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) a[r] = xr[r][k];
+#pragma unroll
+            for (int c = 0; c < 5; ++c) b[c] = xc[c][k];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int c = 0; c < 5; ++c) {
+                    const float u = a[r] - b[c];
+                    acc[r][c] = __builtin_fmaf(u, u, acc[r][c]);
+                }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 5; ++c) {
+                const int rr = h + ty + 8 * r, il = (rr >> 5) * 64 + m * 32 + (rr & 31);
+                float *p = St + rr * kLineLd + tx + 32 * c + (__float_as_int(rowinfo[il].w) & 3);
+                if (c >= c0 && *p == -1.f) *p = acc[r][c];
+            }
+    }
+}
+
+template <int MAP, bool STATS, bool TILED>
+__global__ __launch_bounds__(kGramThreads, 3) void edm_matrix_kernel(MapGeom g, const uint16_t *__restrict__ hi,
+                                                                 const uint16_t *__restrict__ lo,
+                                                                 const float *__restrict__ norms,
+                                                                 const float *__restrict__ inv,
+                                                                 const unsigned *__restrict__ near, int64_t n,
+                                                                 int64_t dpad, const float *__restrict__ X, int64_t d, int64_t ldx,
+                                                                 float *__restrict__ D, unsigned long long *slots) {
+    constexpr int T = 128, NP = 2, S = 2, EX = TILED ? 0 : 1, CB = 4 + EX;
+    constexpr int PER = 4 + CB, TOT = NP * PER, LPW = (TOT + 3) / 4, BUF = TOT * 64;
+    constexpr size_t LDS = S * BUF * 16 > 64 * kLineLd * 4 ? S * BUF * 16 : 64 * kLineLd * 4;
+    uint64_t lin;
+    int TX, TY;
+    if (MAP == MAP_LAMBDA) {
+        lin = launch_index();
+        if (lin >= g.G) return;
+        const uint32_t id = xcd_remap(uint32_t(lin), uint32_t(g.G));
+        if (!lambda2(lambda2_patch_to_xfast(id, g.lg, 3, 4), g.lg, g.nb, TX, TY)) return;
+        if (SMX_CHECKED && !smx_check(0 <= TX && TX <= TY && TY < g.nb, kCheckMap)) return;
+    } else if (!tile2_of<MAP, true>(g, lin, TX, TY)) {
+        return;
+    }
+    __shared__ __attribute__((aligned(16))) uint4 Lb[LDS / 16];
+    // per row: norm, -2 / scale, LDS offset of column 0 in its pass, s_i
+    __shared__ __attribute__((aligned(16))) float4 rowinfo[T];
+    // ... and where its piece begins: in D, and in its LDS row (floats)
+    struct __attribute__((aligned(16))) RowOut {
+        float *to;
+        int from, pad;
+    };
+    __shared__ RowOut rowout[T];
+    __shared__ float nB[kLineCols], iB[kLineCols];
+    __shared__ int nflag, flag[kLineList];
+    auto shift = [&](int il) { return __float_as_int(rowinfo[il].w); };
+
+    const int t = threadIdx.x;
+    const int lane = t & 63, w = t >> 6, wm = w >> 1, wn = w & 1;
+    const int64_t I0 = int64_t(TX) * T, J0 = int64_t(TY) * T;
+    const bool diag = TX == TY;
+
+    auto stats = [&]() {
+        if (!STATS) return;
+        __shared__ unsigned long long red[2][kGramThreads / kWave];
+        unsigned long long cnt, cs;
+        tile_pairs_le_stats<kGramThreads>(I0, J0, T, T, n, cnt, cs);
+        const unsigned long long c = block_sum<unsigned long long, kGramThreads>(cnt, red[0]);
+        const unsigned long long h = block_sum<unsigned long long, kGramThreads>(cs, red[1]);
+        if (t == 0) stats_add(slots, lin, c, h);
+    };
+    const int nst = int(dpad / 16);
+    const int64_t KB = dpad / 16, rbmax = gram_rows(n) / 32 - 1;
+    const uint4 *hi4 = reinterpret_cast<const uint4 *>(hi), *lo4 = reinterpret_cast<const uint4 *>(lo);
+    const int64_t ra = I0 / 32, rc = J0 / 32 - EX;
+    auto issue = [&](int st) {
+        line_issue<NP, CB>(Lb + (st % S) * BUF, hi4, lo4, ra, rc, rbmax, KB, st, w, lane);
+    };
+    issue(0);
+    issue(1);  // d > 16: two stages at least
+    {
+        // more than one sampled pair in 50 near: every block takes the difference form
+        const unsigned c = wave_sum(near[lane]);
+        if (50 * c > unsigned(kEdmSamples)) {
+            wait_vm<0>();  // the stages' writes are done before the panels take their place
+            __syncthreads();
+            float *As = reinterpret_cast<float *>(Lb);
+            static_assert(LDS >= 2 * 128 * kEdmLd * 4, "the difference form's panels fit");
+            if ((ldx & 3) == 0 && d % kEdmKc == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0)
+                edm_diff_tile<8, true, TILED>(As, As + 128 * kEdmLd, TX, TY, X, n, d, ldx, D);
+            else
+                edm_diff_tile<8, false, TILED>(As, As + 128 * kEdmLd, TX, TY, X, n, d, ldx, D);
+            stats();
+            return;
+        }
+    }
+    const int eoff = int((reinterpret_cast<uintptr_t>(D) >> 2) & 31);
+    for (int x = t; x < T; x += kGramThreads) {
+        const int64_t i = I0 + x;
+        const int64_t a = i * n - (i * (i - 1)) / 2 - i + J0;  // element of column J0
+        const int s = TILED ? 0 : int(a + eoff) & 31, r = (x >> 6) * 32 + (x & 31);
+        rowinfo[x] = make_float4(i < n ? norms[i] : 0.f, i < n ? -2.f * inv[i] : 0.f,
+                                 __int_as_float(r * kLineLd + (s & 3)), __int_as_float(s));
+        rowout[x] = {D + (a - s), 32 - (s & ~3), 0};
+    }
+    for (int x = t; x < kLineCols; x += kGramThreads) {
+        const int64_t j = J0 - 32 + x;
+        nB[x] = j >= 0 && j < n ? norms[j] : 0.f;
+        iB[x] = j >= 0 && j < n ? inv[j] : 0.f;
+    }
+
+    // wave (wm, wn): rows 64 wm .., columns 64 wn .. as 2 x 2 products, and of the extra
+    // column block the 32 rows 64 wm + 32 wn ..
+    f32x16_t acc[2][2], ext;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        ext[e] = 0.f;
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) acc[m][c][e] = 0.f;
+    }
+    const uint32_t ring = lds_addr(Lb);
+    // a stage's slot is filled again as soon as every wave has its fragments
+    for (int st = 0; st < nst; ++st) {
+        if (st + 1 < nst) wait_vm<LPW>();
+        else wait_vm<0>();
+        __builtin_amdgcn_s_barrier();
+        const uint32_t cur = ring + uint32_t((st % S) * BUF) * 16u + uint32_t(lane) * 16u;
+        bf16x8_t a[NP][2], b[NP][2], x[NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const uint32_t at0 = cur + uint32_t(p * PER) * 1024u;
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                a[p][m] = lds_frag(at0 + uint32_t(wm * 2 + m) * 1024u);
+                b[p][m] = lds_frag(at0 + uint32_t(4 + EX + wn * 2 + m) * 1024u);
+            }
+            if constexpr (EX != 0) x[p] = lds_frag(at0 + 4u * 1024u);
+        }
+        lds_wait<NP, 2>(a, b);
+        if constexpr (EX != 0) {
+#pragma unroll
+            for (int p = 0; p < NP; ++p) asm_use(x[p]);
+        }
+        __builtin_amdgcn_s_barrier();
+        if (st + 2 < nst) issue(st + 2);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {  // hi hi, hi lo, lo hi
+            const int pa = q == 2, pb = q == 1;
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) acc[m][c] = line_mfma(a[pa][m], b[pb][c], acc[m][c]);
+            if constexpr (EX != 0) ext = line_mfma(wn ? a[pa][1] : a[pa][0], x[pb], ext);
+        }
+    }
+
+    // Epilogue, two passes of 64 rows (32 of each half) staged in the idle ring at
+    // LDS column 32 + (j - J0) + (s_i mod 4), so that a row's line starts are 16-byte
+    // aligned there too.
+    float *St = reinterpret_cast<float *>(Lb);
+    const bool edge = TILED || TX + 1 >= TY || J0 + T >= n || I0 + T > n;
+    // pairs i < j < n: column - row > -dIJ, column below `past`
+    const int dIJ = (TY - TX > 1 ? 2 : TY - TX) * T - 32, past = n - J0 < T ? int(n - J0) + 32 : kLineCols;
+    __syncthreads();     // rowinfo, nB, iB and at are other threads' work (the k loop's barriers order no LDS writes)
+    float nb[3], ib[3];  // this lane's columns: two of the wave's 64, one of the extra block
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const int col = c < 2 ? 32 + wn * 64 + c * 32 + (lane & 31) : lane & 31;
+        nb[c] = nB[col];
+        ib[c] = iB[col];
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        __syncthreads();
+        if (t == 0) nflag = 0;
+        __syncthreads();
+        // FULL: every element is a pair of the tile
+        auto rows = [&](auto full) {
+            constexpr bool FULL = decltype(full)::value;
+            uint32_t left = 0;  // bit e: this lane's row e holds a pair for the list
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int il = wm * 64 + m * 32 + (e & 3) + 4 * (lane >> 5) + 8 * (e >> 2);
+                const float4 ri = rowinfo[il];
+                float *row = St + __float_as_int(ri.z);
+                auto put = [&](int c, int col, float gv) {
+                    const float sum = ri.x + nb[c];
+                    float v;
+                    // (x_i - 2 g) + x_j: one rounding at the sum's size less than the sum first
+                    v = __builtin_fmaf(gv * ri.y, ib[c], ri.x) + nb[c];
+                    // v >= kEdmNear sum and finite, as one comparison of the difference's bits
+                    const uint32_t far = __float_as_uint(__builtin_fmaf(-kEdmNear, sum, v));
+                    bool bad = far >= 0x7f800000u;
+                    if (!FULL) {
+                        const int ij = col - il + dIJ;  // j - i, or above 0 with it
+                        v = ij > 0 && col < past ? v : 0.f;
+                        bad = bad && ij > 0 && col < past;
+                        // the diagonal: exactly 0, or what a point that is not finite gives
+                        bad = bad || (ij == 0 && col < past && !(sum < __builtin_inff()));
+                    }
+                    v = bad ? -1.f : v;  // to be summed as differences
+                    left |= uint32_t(bad) << e;
+                    row[col] = v;
+                };
+#pragma unroll
+                for (int c = 0; c < 2; ++c) put(c, 32 + wn * 64 + c * 32 + (lane & 31), acc[m][c][e]);
+                if (EX && wn == m) put(2, lane & 31, ext[e]);
+                mem_order();  // one row's LDS operands at a time
+            }
+            while (left != 0) {
+                const int e = __builtin_ctz(left);
+                left &= left - 1;
+                const int rl = (e & 3) + 4 * (lane >> 5) + 8 * (e >> 2);
+                const int at = __float_as_int(rowinfo[wm * 64 + m * 32 + rl].z);
+                for (int c = 0; c < 2 + (EX && wn == m); ++c) {
+                    const int col = c < 2 ? 32 + wn * 64 + c * 32 + (lane & 31) : lane & 31;
+                    if (St[at + col] == -1.f) {
+                        const int f = atomicAdd(&nflag, 1);
+                        if (f < kLineList) flag[f] = (wm * 32 + rl) << 8 | col;
+                    }
+                }
+            }
+        };
+        if (edge) rows(std::false_type{});
+        else rows(std::true_type{});
+        __syncthreads();
+        if (nflag != 0) {
+            // pairs to be summed as differences: listed, or too many for the list
+            if (nflag <= kLineList) {
+                if (t < nflag) {
+                    const int r = flag[t] >> 8, col = flag[t] & 255, il = (r >> 5) * 64 + m * 32 + (r & 31);
+                    St[r * kLineLd + col + (shift(il) & 3)] = edm_pair(X + (I0 + il) * ldx, X + (J0 - 32 + col) * ldx, d);
+                }
+            } else {
+                edm_pass_diff(St, rowinfo, X, n, d, ldx, I0, J0, m, 1 - EX, t);
+            }
+            __syncthreads();
+        }
+        if (TILED) {
+            const uint64_t rank = uint64_t(TY) * (uint64_t(TY) + 1) / 2 + uint64_t(TX);
+#pragma unroll
+            for (int it = 0; it < 8; ++it) {
+                const int r = w * 16 + 2 * it + (lane >> 5), cl = 4 * (lane & 31), il = (r >> 5) * 64 + m * 32 + (r & 31);
+                float4 v = *reinterpret_cast<const float4 *>(St + r * kLineLd + 32 + cl);
+                const int64_t i = I0 + il, j = J0 + cl;
+                v.x = i < n && j + 0 < n && j + 0 >= i ? v.x : 0.f;
+                v.y = i < n && j + 1 < n && j + 1 >= i ? v.y : 0.f;
+                v.z = i < n && j + 2 < n && j + 2 >= i ? v.z : 0.f;
+                v.w = i < n && j + 3 < n && j + 3 >= i ? v.w : 0.f;
+                store4<true>(D + rank * uint64_t(T * T) + uint64_t(il * T + cl), v);
+            }
+        } else if (!edge) {
+            // a wave writes two rows, four whole lines each, per instruction
+            const RowOut *out = rowout + (w >> 1) * 64 + m * 32 + (w & 1) * 16 + (lane >> 5);
+            const float *sr = St + (w * 16 + (lane >> 5)) * kLineLd + 4 * (lane & 31);
+#pragma unroll
+            for (int it = 0; it < 8; ++it) {
+                const RowOut o = out[2 * it];
+                const float4 v = *reinterpret_cast<const float4 *>(sr + 2 * it * kLineLd + o.from);
+                store4<true>(o.to + 4 * (lane & 31), v);
+            }
+        } else {
+            for (int q = 0; q < 16; ++q) {
+                const int r = w * 16 + q, il = (r >> 5) * 64 + m * 32 + (r & 31), s = shift(il);
+                const int64_t i = I0 + il;
+                if (i >= n) continue;
+                const int64_t first = diag || J0 - s < i ? i : J0 - s, last = J0 + T >= n ? n : J0 + T - s;
+                for (int col = lane; col < kLineCols; col += 64) {
+                    const int64_t j = J0 - 32 + col;
+                    if (j >= first && j < last) rowout[il].to[j - (J0 - s)] = St[r * kLineLd + col + (s & 3)];
+                }
+            }
+        }
+    }
+    stats();
+}
+
+// FP32 operands.  The centre is the mean of eight rows (0 where that is not finite):
+// it cancels in every pair, and removes what the points have in common.  Per row the
+// centred norm (summed in FP64), the power-of-two scale and the scaled coordinates
+// as FP16 hi + lo in fragment order.  2^lgl lanes share a row, eight coordinates a
+// lane at a time (in registers between the two uses while d <= 512); a block makes
+// 256 >> lgl rows.  The blocks also look at kEdmSampleBlocks x 16 pairs and count those
+// that the Gram form would have to leave to differences.
+__global__ __launch_bounds__(256) void edm_prep_kernel(const float *__restrict__ X, int64_t n, int64_t d, int64_t ldx,
+                                                      int64_t dpad, int64_t npad, int lgl, uint4 *__restrict__ hi,
+                                                      uint4 *__restrict__ lo, float *__restrict__ norms,
+                                                      float *__restrict__ inv, unsigned *__restrict__ near) {
+    extern __shared__ float centre[];  // [d]
+    __shared__ unsigned found[16];
+    for (int64_t k = threadIdx.x; k < d; k += 256) {
+        float s = 0.f;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s += X[(q * n / 8) * ldx + k];
+        s *= 0.125f;
+        centre[k] = __builtin_fabsf(s) < __builtin_inff() ? s : 0.f;
+    }
+    __syncthreads();
+    const int64_t KB = dpad / 16, nq = dpad / 8;
+    const int lanes = 1 << lgl, l = int(threadIdx.x) & (lanes - 1);
+    const int64_t row = (int64_t(blockIdx.x) << (8 - lgl)) + (threadIdx.x >> lgl);
+    const bool in = row < n;
+    double x[8];
+    auto load8 = [&](int64_t q) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int64_t k = 8 * q + e;
+            x[e] = in && k < d ? double(X[row * ldx + k]) - double(centre[k]) : 0.0;
+        }
+    };
+    double acc = 0.0, big = 0.0;
+    for (int64_t q = l; q < nq; q += lanes) {
+        load8(q);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            acc = __builtin_fma(x[e], x[e], acc);
+            const double a = __builtin_fabs(x[e]);
+            big = a > big || a != a ? a : big;
+        }
+    }
+    for (int o = lanes / 2; o > 0; o >>= 1) {
+        acc += __shfl_xor(acc, o, kWave);
+        const double v = __shfl_xor(big, o, kWave);
+        big = v > big || v != v ? v : big;
+    }
+    // c big in [2^13, 2^14): FP16 ends at 2^16.  Not a number where the row is not.
+    int ex = 0;
+    (void)__builtin_frexp(big, &ex);
+    const double c = !(big < double(__builtin_inff())) ? __builtin_nan("") : big == 0.0 ? 1.0 : __builtin_ldexp(1.0, 14 - ex);
+    if (row < npad)
+        for (int64_t q = l; q < nq; q += lanes) {
+            if (nq > lanes) load8(q);
+            uint32_t h[4], w[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float x0 = in ? float(x[2 * e] * c) : 0.f, x1 = in ? float(x[2 * e + 1] * c) : 0.f;
+                const _Float16 h0 = _Float16(x0), h1 = _Float16(x1);
+                const _Float16 l0 = _Float16(x0 - float(h0)), l1 = _Float16(x1 - float(h1));
+                h[e] = uint32_t(__builtin_bit_cast(uint16_t, h0)) | uint32_t(__builtin_bit_cast(uint16_t, h1)) << 16;
+                w[e] = uint32_t(__builtin_bit_cast(uint16_t, l0)) | uint32_t(__builtin_bit_cast(uint16_t, l1)) << 16;
+            }
+            const int64_t slot = ((row >> 5) * KB + (q >> 1)) * 64 + (row & 31) + 32 * (q & 1);
+            hi[slot] = make_uint4(h[0], h[1], h[2], h[3]);
+            lo[slot] = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    if (l == 0 && in) {
+        norms[row] = float(acc);
+        inv[row] = float(1.0 / c);
+    }
+    // 16 lanes a sampled pair
+    for (int sb = int(blockIdx.x); sb < kEdmSampleBlocks; sb += int(gridDim.x)) {
+        const uint64_t z = mix64(uint64_t(sb) * 16 + (threadIdx.x >> 4));
+        const int64_t i = int64_t(uint32_t(z) % uint64_t(n)), j = int64_t(uint32_t(z >> 32) % uint64_t(n));
+        double s = 0.0, g = 0.0;
+        for (int64_t k = threadIdx.x & 15; k < d; k += 16) {
+            const double m = centre[k], a = double(X[i * ldx + k]) - m, b = double(X[j * ldx + k]) - m;
+            s += a * a + b * b;
+            g += (a - b) * (a - b);
+        }
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) {
+            s += __shfl_xor(s, o, kWave);
+            g += __shfl_xor(g, o, kWave);
+        }
+        if ((threadIdx.x & 15) == 0) found[threadIdx.x >> 4] = i != j && !(g >= double(kEdmNear) * s) ? 1u : 0u;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            unsigned f = 0;
+            for (int q = 0; q < 16; ++q) f += found[q];
+            near[sb] = f;
+        }
+        __syncthreads();
+    }
+}
+
+int launch_edm_prep(const float *X, int64_t n, int64_t d, int64_t ldx, int64_t dpad, unsigned *near, uint16_t *hi,
+                    uint16_t *lo, float *norms, float *inv, hipStream_t s) {
+    const int64_t npad = gram_rows(n);
+    int lgl = 2;  // lanes a row: one per eight coordinates, 4 to 64
+    while (lgl < 6 && (int64_t(1) << lgl) < dpad / 8) ++lgl;
+    const int64_t rows = 256 >> lgl;
+    prof_begin(K_GRAM_PREP, s);
+    hipLaunchKernelGGL(edm_prep_kernel, dim3(uint32_t((npad + rows - 1) / rows)), dim3(256), size_t(d) * 4, s, X, n, d, ldx,
+                       dpad, npad, lgl, reinterpret_cast<uint4 *>(hi), reinterpret_cast<uint4 *>(lo), norms, inv, near);
+    prof_end(K_GRAM_PREP, s);
+    return check_launch("edm prep");
+}
+
+template <int MAP, bool TILED>
+static void go_lines(const MapGeom &g, const uint16_t *hi, const uint16_t *lo, const float *norms, const float *inv,
+                     const unsigned *near, int64_t n, int64_t dpad, const float *X, int64_t d, int64_t ldx, float *D, unsigned long long *slots,
+                     hipStream_t s) {
+    const dim3 grid = MAP == MAP_BBOX ? dim3(g.nb, g.nb, 1) : grid_for(g.G, kGramThreads);
+    if (slots)
+        hipLaunchKernelGGL((edm_matrix_kernel<MAP, true, TILED>), grid, dim3(kGramThreads), 0, s, g, hi, lo, norms,
+                           inv, near, n, dpad, X, d, ldx, D, slots);
+    else
+        hipLaunchKernelGGL((edm_matrix_kernel<MAP, false, TILED>), grid, dim3(kGramThreads), 0, s, g, hi, lo, norms,
+                           inv, near, n, dpad, X, d, ldx, D, slots);
+}
+
+int launch_edm_matrix(const MapGeom &g, const uint16_t *hi, const uint16_t *lo, const float *norms, const float *inv,
+                      const unsigned *near, int64_t n, int64_t dpad, const float *X, int64_t d, int64_t ldx, float *D,
+                      unsigned long long *slots, bool tiled, hipStream_t s) {
+    prof_begin(K_EDM_DIFF, s);
+    for_each_launch(g, [&](auto M, const MapGeom &gg) {
+        constexpr int MAPK = decltype(M)::value;
+        if (tiled) go_lines<MAPK, true>(gg, hi, lo, norms, inv, near, n, dpad, X, d, ldx, D, slots, s);
+        else go_lines<MAPK, false>(gg, hi, lo, norms, inv, near, n, dpad, X, d, ldx, D, slots, s);
+    });
+    prof_end(K_EDM_DIFF, s);
+    return check_launch("edm_packed (fp32, matrix form)");
 }
 
 SMX_CHECK_READER(check_flags_gram)

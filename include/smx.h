@@ -239,7 +239,7 @@ int smx_simplex_count(int m, int64_t n, int rho, int map, int strict, int64_t *d
  *         (hi = bf16(x), lo = bf16(x - hi)), accumulate in FP32, add FP32 norms
  *         |x|^2, clamp the result at 0.
  *         FP32_DIFF runs on the matrix cores from n = 8192 and d = 36 (n = 5120
- *         from d = 64) on: a centred Gram form of FP16 hi + lo pairs (2^-23) with
+ *         from d = 65) on: a centred Gram form of FP16 hi + lo pairs (2^-23) with
  *         FP32 sums for the pairs it is exact for, the difference form for the
  *         others (near points, NaN, infinities).
  *   d_ws  smx_workspace_bytes(1, n, d, prec, map) bytes.  For FP32_DIFF, NULL (or,

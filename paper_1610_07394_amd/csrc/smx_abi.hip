@@ -184,11 +184,13 @@ static EdmWs edm_ws(int64_t n, int64_t d, int prec) {
     return w;
 }
 // FP32 on the matrix cores: where the products outweigh the preparation and the
-// wider tiles (a caller may skip the workspace below the first n).  ms, matrix / difference form: n = 4096 d = 64 0.042 / 0.034, n = 6000 d
-// = 32 0.061 / 0.054, d = 64 0.062 / 0.094, n = 9001 d = 37 0.094 / 0.199, n = 65536 d =
-// 64 2.6 / 6.3; with every second pair near (difference form in either) n = 9001 d =
-// 37 0.16 / 0.21, n = 65536 d = 64 6.3 / 6.2.  d <= 8192: the centre lies in LDS.
-static bool edm_fp32_matrix(int64_t n, int64_t d) { return n >= (d >= 64 ? 5120 : 8192) && d >= 36 && d <= 8192; }
+// wider tiles (a caller may skip the workspace below the first n).  us, matrix /
+// difference form: n = 6000, d = 64 61 / 59, d = 65 66 / 86; n = 8192, d = 36 73 / 109,
+// n = 9001, d = 36 89 / 122, n = 40000, d = 64 1050 / 2430; eight tight
+// clusters (the difference tile in either) n = 9001, d = 37 164 / 143, n = 65536, d = 64
+// 6780 / 6500.
+// d <= 8192: the centre lies in LDS.
+static bool edm_fp32_matrix(int64_t n, int64_t d) { return n >= (d > 64 ? 5120 : 8192) && d >= 36 && d <= 8192; }
 
 struct TripWs {
     size_t eslots, at_stats, lj_stats, g64, total;
@@ -480,10 +482,12 @@ static int edm_run(bool tiled, const float *d_X, int64_t n, int64_t d, int64_t l
     const int tile = tiled ? kEdmTiledTile : fp32 && !matrix ? edm_diff_tile(n) : gram_tile(n);
     MapGeom g;
     if (!make_geom(2, (n + tile - 1) / tile, map, g)) return g_status;
-    // where nb is no power of two, lambda2 from above filters up to three ids in four, in
-    // stretches that leave XCDs idle; from below lists the same tiles (statistics keep
-    // the map's own count of blocks)
-    if (matrix && map == MAP_LAMBDA && d_stats == nullptr && !pow2(g.nb) && !make_geom(2, g.nb, MAP_BELOW, g)) return g_status;
+    // FP32: where nb is no power of two, lambda2 from above filters up to three ids in
+    // four, in stretches that leave XCDs idle; from below lists the same tiles
+    // (statistics keep the map's own count of blocks).  Difference form, us: n = 5000, d
+    // = 32 49 -> 28; 9000, 100 383 -> 226; 20000, 64 1216 -> 606; 33000, 256 9870 -> 5401;
+    // one tile per CU or less (n = 600) 9.3 and 9.1
+    if (fp32 && map == MAP_LAMBDA && d_stats == nullptr && !pow2(g.nb) && !make_geom(2, g.nb, MAP_BELOW, g)) return g_status;
     char *ws = reinterpret_cast<char *>(d_ws);
     unsigned long long *slots = d_stats ? reinterpret_cast<unsigned long long *>(ws + w.slots) : nullptr;
     int rc;

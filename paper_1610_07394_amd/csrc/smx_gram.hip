@@ -227,10 +227,15 @@ __global__ __launch_bounds__(kGramThreads, 4) void edm_gram_kernel(MapGeom g, co
         // beyond L2 4.2 -> 0.8 GB plain, 8.6 -> 2.8 GB split.  Column-major order
         // (w_y fastest, whose concurrent tiles extend the same packed rows) is
         // the faster one for the stores alone, but with the non-temporal stores
-        // the patches took 5-10% less time at d = 512.
+        // the patches took 5-10% less time at d = 512.  Where nb is no power of two the
+        // filtered ids lie in stretches that would empty some XCDs' ranges, and runs of 16
+        // ids are dealt in turn instead, us: n = 16484, d = 300 268 -> 227 plain, 536 -> 333
+        // split; n = 20000, d = 64 250 -> 235 and 300 -> 247; n = 5000, d = 32 28 -> 20 and
+        // 34 -> 22.
         lin = launch_index();
         if (lin >= g.G) return;
-        const uint32_t id = xcd_remap(uint32_t(lin), uint32_t(g.G));
+        const uint32_t id = (g.nb & (g.nb - 1)) == 0 ? xcd_remap(uint32_t(lin), uint32_t(g.G))
+                                                     : xcd_deal(uint32_t(lin), uint32_t(g.G), 4);
         if (!lambda2(SPLIT ? lambda2_patch_to_xfast(id, g.lg, 4, 3) : lambda2_patch_to_xfast(id, g.lg, 3, 4), g.lg,
                      g.nb, TX, TY))
             return;
@@ -452,8 +457,8 @@ int launch_edm_gram(const MapGeom &g, int tile, const uint16_t *hi, const uint16
 // the products), and all stores but those at the ends of a packed row are whole
 // lines, streaming.
 //
-// n = 65536, d = 64: 6.3 -> 2.6 ms (3.3 TB/s of stores); 20000, 100: 2.4 -> 0.38; 9001,
-// 37: 0.20 -> 0.09.
+// n = 65536, d = 64: 6.3 -> 2.6 ms (3.3 TB/s of stores); 20000, 100: 1.1 -> 0.37; 9001,
+// 37: 0.12 -> 0.09.
 constexpr int kLineCols = 160;           // 32 + 128 columns of a tile row
 constexpr int kLineLd = kLineCols + 4;   // LDS row: shifted by s_i mod 4 floats
 constexpr int kLineList = 128;

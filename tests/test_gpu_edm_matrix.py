@@ -1,5 +1,5 @@
 """FP32 distances on the matrix cores (n >= 8192 with d >= 36, n >= 5120 with d >=
-64, given the workspace): every pair to FP32 accuracy, the difference form being
+65, given the workspace): every pair to FP32 accuracy, the difference form being
 the other path (a workspace of 32768 bytes selects it).
 
 Tolerance: |D^ - D| / D <= 1e-5 as for the difference form.  A kept Gram value is
@@ -55,7 +55,7 @@ def _data(kind, n, d, seed):
 
 
 # first sizes, tile edges, one row past a tile; d at the ends of a k block
-@pytest.mark.parametrize("n,d", [(5119, 64), (5120, 64), (5121, 65), (8191, 37), (8192, 36), (8193, 37), (8320, 48), (8325, 100)])
+@pytest.mark.parametrize("n,d", [(5119, 65), (5120, 65), (5121, 66), (6000, 64), (8191, 37), (8192, 36), (8193, 37), (8320, 48), (8325, 100)])
 def test_sizes_and_maps(n, d):
     print(f"edm matrix n={n} d={d}", flush=True)
     X = _data("few_near", n, d, seed=n + d)

@@ -52,9 +52,39 @@ int launch_stats_finalize(const unsigned long long *slots, uint64_t launched, in
     return check_launch("stats finalize");
 }
 
-template <int MAP, bool STRICT>
-__global__ __launch_bounds__(kMapThreads) void map2_kernel(MapGeom g, int64_t n, int rho, int lgrho,
-                                                          int32_t *tiles, unsigned long long *slots) {
+// Sum of a block's counts and checksums into its statistics slot.
+template <int NT>
+__device__ __forceinline__ void map_stats(unsigned cnt, unsigned long long cs, unsigned long long *slots, uint64_t lin) {
+    if constexpr (NT == kWave) {
+        const unsigned c = wave_sum(cnt);
+        const unsigned long long h = wave_sum(cs);
+        if (threadIdx.x == 0) stats_add(slots, lin, c, h);
+    } else {
+        __shared__ unsigned redc[NT / kWave];
+        __shared__ unsigned long long redh[NT / kWave];
+        const unsigned c = block_sum<unsigned, NT>(cnt, redc);
+        const unsigned long long h = block_sum<unsigned long long, NT>(cs, redh);
+        if (threadIdx.x == 0) stats_add(slots, lin, c, h);
+    }
+}
+
+// The elements of a tile: a thread holds the coordinates after i, which fix all of
+// the id but i, and walks i (2^lgout coordinates after i; with fewer than NT of
+// them, NT / 2^lgout threads share one set and take i in turn).  The id's products and
+// its division, once per element, took as long as the SplitMix64 sums that bound
+// the rest (two 64-bit products an element).  m = 3, n = 1024, rho = 8, strict, 3.6e5
+// tiles: 479 -> 186 us; m = 2, n = 32768, rho = 16 2226 -> 648; m = 4, n = 200, rho = 4
+// 1433 -> 440.
+template <int NT, typename F>
+__device__ __forceinline__ void tile_walk(int lgout, F &&f) {
+    const int lgw = lgout < (NT == 64 ? 6 : 8) ? lgout : (NT == 64 ? 6 : 8);
+    const int step = NT >> lgw, first = int(threadIdx.x) >> lgw;
+    for (int o = int(threadIdx.x) & ((1 << lgw) - 1); o < (1 << lgout); o += 1 << lgw) f(o, first, step);
+}
+
+template <int MAP, bool STRICT, int NT>
+__global__ __launch_bounds__(NT) void map2_kernel(MapGeom g, int64_t n, int rho, int lgrho, int32_t *tiles,
+                                                  unsigned long long *slots) {
     uint64_t lin;
     int X = -1, Y = -1;
     const bool ok = tile2_of<MAP, false>(g, lin, X, Y);
@@ -64,26 +94,23 @@ __global__ __launch_bounds__(kMapThreads) void map2_kernel(MapGeom g, int64_t n,
         tiles[2 * lin + 1] = ok ? Y : -1;
     }
     if (!ok || slots == nullptr) return;
-    __shared__ unsigned long long red[2][kMapThreads / kWave];
-    unsigned long long cnt = 0, cs = 0;
+    unsigned cnt = 0;
+    unsigned long long cs = 0;
     const int64_t i0 = int64_t(X) * rho, j0 = int64_t(Y) * rho;
-    const int rmask = rho - 1;
-    for (int e = threadIdx.x; e < rho * rho; e += kMapThreads) {
-        const int64_t i = i0 + (e >> lgrho), j = j0 + (e & rmask);
-        const bool v = j < n && (STRICT ? i < j : i <= j);
-        if (v) {
+    tile_walk<NT>(lgrho, [&](int o, int first, int step) {
+        const int64_t j = j0 + o, end = STRICT ? j : j + 1;  // i < end
+        const int m = j >= n ? 0 : int(end - i0 < rho ? end - i0 : rho);
+        for (int a = first; a < m; a += step) {
             ++cnt;
-            cs += mix64(STRICT ? id_pair_lt(i, j) : id_pair_le(i, j, uint64_t(n)));
+            cs += mix64(STRICT ? id_pair_lt(i0 + a, j) : id_pair_le(i0 + a, j, uint64_t(n)));
         }
-    }
-    const unsigned long long c = block_sum<unsigned long long, kMapThreads>(cnt, red[0]);
-    const unsigned long long h = block_sum<unsigned long long, kMapThreads>(cs, red[1]);
-    if (threadIdx.x == 0) stats_add(slots, lin, c, h);
+    });
+    map_stats<NT>(cnt, cs, slots, lin);
 }
 
-template <int MAP, bool STRICT>
-__global__ __launch_bounds__(kMapThreads) void map3_kernel(MapGeom g, int64_t n, int rho, int lgrho,
-                                                          int32_t *tiles, unsigned long long *slots) {
+template <int MAP, bool STRICT, int NT>
+__global__ __launch_bounds__(NT) void map3_kernel(MapGeom g, int64_t n, int rho, int lgrho, int32_t *tiles,
+                                                  unsigned long long *slots) {
     uint64_t lin;
     int X = -1, Y = -1, Z = -1;
     const bool ok = tile3_of<MAP, false>(g, lin, X, Y, Z);
@@ -94,26 +121,25 @@ __global__ __launch_bounds__(kMapThreads) void map3_kernel(MapGeom g, int64_t n,
         tiles[3 * lin + 2] = ok ? Z : -1;
     }
     if (!ok || slots == nullptr) return;
-    __shared__ unsigned long long red[2][kMapThreads / kWave];
-    unsigned long long cnt = 0, cs = 0;
+    unsigned cnt = 0;
+    unsigned long long cs = 0;
     const int64_t i0 = int64_t(X) * rho, j0 = int64_t(Y) * rho, k0 = int64_t(Z) * rho;
-    const int rmask = rho - 1;
-    for (int e = threadIdx.x; e < rho * rho * rho; e += kMapThreads) {
-        const int64_t i = i0 + (e >> (2 * lgrho)), j = j0 + ((e >> lgrho) & rmask), k = k0 + (e & rmask);
-        const bool v = k < n && (STRICT ? (i < j && j < k) : (i <= j && j <= k));
-        if (v) {
+    tile_walk<NT>(2 * lgrho, [&](int o, int first, int step) {
+        const int64_t j = j0 + (o >> lgrho), k = k0 + (o & (rho - 1)), end = STRICT ? j : j + 1;
+        const bool in = k < n && (STRICT ? j < k : j <= k);
+        const int m = !in ? 0 : int(end - i0 < rho ? end - i0 : rho);
+        const uint64_t id = (STRICT ? id_trip_lt(0, j, k) : id_trip_le(0, j, k)) + uint64_t(i0);
+        for (int a = first; a < m; a += step) {
             ++cnt;
-            cs += mix64(STRICT ? id_trip_lt(i, j, k) : id_trip_le(i, j, k));
+            cs += mix64(id + a);
         }
-    }
-    const unsigned long long c = block_sum<unsigned long long, kMapThreads>(cnt, red[0]);
-    const unsigned long long h = block_sum<unsigned long long, kMapThreads>(cs, red[1]);
-    if (threadIdx.x == 0) stats_add(slots, lin, c, h);
+    });
+    map_stats<NT>(cnt, cs, slots, lin);
 }
 
-template <int MAP, bool STRICT>
-__global__ __launch_bounds__(kMapThreads) void map4_kernel(MapGeom g, int64_t n, int rho, int lgrho,
-                                                          int32_t *tiles, unsigned long long *slots) {
+template <int MAP, bool STRICT, int NT>
+__global__ __launch_bounds__(NT) void map4_kernel(MapGeom g, int64_t n, int rho, int lgrho, int32_t *tiles,
+                                                  unsigned long long *slots) {
     uint64_t lin;
     int X[4] = {-1, -1, -1, -1};
     const bool ok = tile4_of<MAP, false>(g, lin, X);
@@ -122,23 +148,23 @@ __global__ __launch_bounds__(kMapThreads) void map4_kernel(MapGeom g, int64_t n,
         for (int d = 0; d < 4; ++d) tiles[4 * lin + d] = ok ? X[d] : -1;
     }
     if (!ok || slots == nullptr) return;
-    __shared__ unsigned long long red[2][kMapThreads / kWave];
-    unsigned long long cnt = 0, cs = 0;
+    unsigned cnt = 0;
+    unsigned long long cs = 0;
     const int64_t i0 = int64_t(X[0]) * rho, j0 = int64_t(X[1]) * rho, k0 = int64_t(X[2]) * rho,
                   l0 = int64_t(X[3]) * rho;
     const int rmask = rho - 1;
-    for (int e = threadIdx.x; e < rho * rho * rho * rho; e += kMapThreads) {
-        const int64_t i = i0 + (e >> (3 * lgrho)), j = j0 + ((e >> (2 * lgrho)) & rmask),
-                      k = k0 + ((e >> lgrho) & rmask), l = l0 + (e & rmask);
-        const bool v = l < n && (STRICT ? (i < j && j < k && k < l) : (i <= j && j <= k && k <= l));
-        if (v) {
+    tile_walk<NT>(3 * lgrho, [&](int o, int first, int step) {
+        const int64_t j = j0 + (o >> (2 * lgrho)), k = k0 + ((o >> lgrho) & rmask), l = l0 + (o & rmask),
+                      end = STRICT ? j : j + 1;
+        const bool in = l < n && (STRICT ? (j < k && k < l) : (j <= k && k <= l));
+        const int m = !in ? 0 : int(end - i0 < rho ? end - i0 : rho);
+        const uint64_t id = (STRICT ? id_quad_lt(0, j, k, l) : id_quad_le(0, j, k, l)) + uint64_t(i0);
+        for (int a = first; a < m; a += step) {
             ++cnt;
-            cs += mix64(STRICT ? id_quad_lt(i, j, k, l) : id_quad_le(i, j, k, l));
+            cs += mix64(id + a);
         }
-    }
-    const unsigned long long c = block_sum<unsigned long long, kMapThreads>(cnt, red[0]);
-    const unsigned long long h = block_sum<unsigned long long, kMapThreads>(cs, red[1]);
-    if (threadIdx.x == 0) stats_add(slots, lin, c, h);
+    });
+    map_stats<NT>(cnt, cs, slots, lin);
 }
 
 // Element count of one tile in closed form: t = elements of a tile edge that
@@ -310,40 +336,51 @@ int launch_decode(int m, const MapGeom &g, unsigned long long *slots, hipStream_
     return check_launch("simplex decode");
 }
 
+// go(strict, threads).  One wave a block (no barrier, a quarter of the waves to launch,
+// more elements a lane to share the outer coordinates) for tiles of up to 1024
+// elements, and of up to 4096 once the blocks alone fill the chip (32 waves on 256
+// CUs); else 256 threads.  us, 64 / 256 threads: m = 3, n = 1024, rho = 8 186 / 375; m = 2, n
+// = 32768, rho = 64 321 / 376; m = 4, n = 256, rho = 8 183 / 220; but m = 3, n = 400, rho = 16
+// (6 670 blocks) 31 / 26.
+template <typename F>
+static void map_threads(int lgtile, uint64_t G, int strict, F &&go) {
+    using Wave = std::integral_constant<int, kWave>;
+    using Wide = std::integral_constant<int, kMapThreads>;
+    const bool wave = lgtile <= (G >= 8192 ? 12 : 10);
+    if (strict && wave) go(std::true_type{}, Wave{});
+    else if (strict) go(std::true_type{}, Wide{});
+    else if (wave) go(std::false_type{}, Wave{});
+    else go(std::false_type{}, Wide{});
+}
+
 template <int MAP>
 static void go_map2(const MapGeom &g, int64_t n, int rho, int lgrho, int strict, int32_t *tiles,
                     unsigned long long *slots, hipStream_t s) {
-    const dim3 grid = MAP == MAP_BBOX ? dim3(g.nb, g.nb, 1) : grid_for(g.G, kMapThreads);
-    if (strict)
-        hipLaunchKernelGGL((map2_kernel<MAP, true>), grid, dim3(kMapThreads), 0, s, g, n, rho, lgrho,
-                           tiles, slots);
-    else
-        hipLaunchKernelGGL((map2_kernel<MAP, false>), grid, dim3(kMapThreads), 0, s, g, n, rho, lgrho,
-                           tiles, slots);
+    auto go = [&](auto STRICT, auto NT) {
+        const dim3 grid = MAP == MAP_BBOX ? dim3(g.nb, g.nb, 1) : grid_for(g.G, NT());
+        hipLaunchKernelGGL((map2_kernel<MAP, STRICT(), NT()>), grid, dim3(NT()), 0, s, g, n, rho, lgrho, tiles, slots);
+    };
+    map_threads(2 * lgrho, g.G, strict, go);
 }
 
 template <int MAP>
 static void go_map3(const MapGeom &g, int64_t n, int rho, int lgrho, int strict, int32_t *tiles,
                     unsigned long long *slots, hipStream_t s) {
-    const dim3 grid = MAP == MAP_BBOX ? dim3(g.nb, g.nb, g.nb) : grid_for(g.G, kMapThreads);
-    if (strict)
-        hipLaunchKernelGGL((map3_kernel<MAP, true>), grid, dim3(kMapThreads), 0, s, g, n, rho, lgrho,
-                           tiles, slots);
-    else
-        hipLaunchKernelGGL((map3_kernel<MAP, false>), grid, dim3(kMapThreads), 0, s, g, n, rho, lgrho,
-                           tiles, slots);
+    auto go = [&](auto STRICT, auto NT) {
+        const dim3 grid = MAP == MAP_BBOX ? dim3(g.nb, g.nb, g.nb) : grid_for(g.G, NT());
+        hipLaunchKernelGGL((map3_kernel<MAP, STRICT(), NT()>), grid, dim3(NT()), 0, s, g, n, rho, lgrho, tiles, slots);
+    };
+    map_threads(3 * lgrho, g.G, strict, go);
 }
 
 template <int MAP>
 static void go_map4(const MapGeom &g, int64_t n, int rho, int lgrho, int strict, int32_t *tiles,
                     unsigned long long *slots, hipStream_t s) {
-    const dim3 grid = grid_for(g.G, kMapThreads);
-    if (strict)
-        hipLaunchKernelGGL((map4_kernel<MAP, true>), grid, dim3(kMapThreads), 0, s, g, n, rho, lgrho,
-                           tiles, slots);
-    else
-        hipLaunchKernelGGL((map4_kernel<MAP, false>), grid, dim3(kMapThreads), 0, s, g, n, rho, lgrho,
-                           tiles, slots);
+    auto go = [&](auto STRICT, auto NT) {
+        const dim3 grid = grid_for(g.G, NT());
+        hipLaunchKernelGGL((map4_kernel<MAP, STRICT(), NT()>), grid, dim3(NT()), 0, s, g, n, rho, lgrho, tiles, slots);
+    };
+    map_threads(4 * lgrho, g.G, strict, go);
 }
 
 int launch_map4(const MapGeom &g, int64_t n, int rho, int strict, int32_t *tiles,

@@ -590,12 +590,13 @@ static int triplet_run(int mode, const float *d_X, int64_t n, int64_t ldx, const
     if (do_lj && (rc = launch_lj(g2, d_X, n, ldx, float(pot->lj_eps), float(pot->lj_sigma),
                                  float(pot->lj_rc * pot->lj_rc), G64, eslots, lj_st, s)))
         return rc;
-    if (d_E != nullptr && (rc = launch_energy_finalize(eslots, d_E, s))) return rc;
+    const bool with_grad = grad && n > 0;
+    if (d_E != nullptr && !with_grad && (rc = launch_energy_finalize(eslots, d_E, s))) return rc;
     if (d_stats != nullptr) {
         if ((rc = launch_stats_finalize(at_st, do_at ? g3.G : 0, d_stats, s))) return rc;
         if ((rc = launch_stats_finalize(lj_st, do_lj ? g2.G : 0, d_stats + 4, s))) return rc;
     }
-    if (grad && n > 0 && (rc = launch_grad_finalize(G64, n, mode == 2 ? d_gradE : nullptr, d_G, s))) return rc;
+    if (with_grad && (rc = launch_grad_finalize(G64, n, mode == 2 ? d_gradE : nullptr, d_G, eslots, d_E, s))) return rc;
     return SMX_OK;
 }
 

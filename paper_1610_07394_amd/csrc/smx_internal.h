@@ -186,8 +186,8 @@ int launch_life(const MapGeom &g, const uint8_t *S, uint8_t *D, int64_t n, unsig
                 hipStream_t s);
 int launch_count_finalize(const unsigned long long *slots, int64_t *out, hipStream_t s);
 int launch_valu_probe(float *out, int64_t blocks, int iters, hipStream_t s);
-int launch_grad_finalize(const double *G64, int64_t n, const double *gradE, float *out,
-                         hipStream_t s);
+int launch_grad_finalize(const double *G64, int64_t n, const double *gradE, float *out, const double *eslots,
+                         double *E, hipStream_t s);  // E nullable
 int launch_scale_grad(const float *G, int64_t n, const double *gradE, float *out, hipStream_t s);
 
 }  // namespace smx

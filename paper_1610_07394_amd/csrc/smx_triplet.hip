@@ -597,9 +597,10 @@ int launch_lj(const MapGeom &g, const float *X, int64_t n, int64_t ldx, float ep
 }
 
 // ---------------------------------------------------------------- finalize
-__global__ void energy_finalize_kernel(const double *eslots, double *E) {
+// E[0..2] = total, AT, LJ from the kSlots slots; kSlots threads.
+__device__ __forceinline__ void energy_sum(const double *eslots, double *E) {
     __shared__ double red[2][kSlots / kWave];
-    const int t = threadIdx.x;  // kSlots threads
+    const int t = threadIdx.x;
     const double a = block_sum<double, kSlots>(eslots[t * kSlotStride + 0], red[0]);
     const double b = block_sum<double, kSlots>(eslots[t * kSlotStride + 1], red[1]);
     if (t == 0) {
@@ -609,6 +610,8 @@ __global__ void energy_finalize_kernel(const double *eslots, double *E) {
     }
 }
 
+__global__ void energy_finalize_kernel(const double *eslots, double *E) { energy_sum(eslots, E); }
+
 int launch_energy_finalize(const double *eslots, double *E, hipStream_t s) {
     prof_begin(K_FINALIZE, s);
     hipLaunchKernelGGL(energy_finalize_kernel, dim3(1), dim3(kSlots), 0, s, eslots, E);
@@ -616,7 +619,17 @@ int launch_energy_finalize(const double *eslots, double *E, hipStream_t s) {
     return check_launch("energy finalize");
 }
 
-__global__ void grad_finalize_kernel(const double *G64, int64_t m, const double *gradE, float *out) {
+// The gradient in FP32, scaled by *gradE when given; with E, one block more sums the
+// energies: as a launch of their own they took 0.9 of the 39 us of a call at n = 500.
+constexpr int kFinalizeThreads = 256;
+static_assert(kFinalizeThreads == kSlots, "energy_sum is one thread a slot");
+
+__global__ void grad_finalize_kernel(const double *G64, int64_t m, const double *gradE, float *out,
+                                     const double *eslots, double *E) {
+    if (E != nullptr && blockIdx.x == gridDim.x - 1) {
+        energy_sum(eslots, E);
+        return;
+    }
     const int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (q >= m) return;
     const double sc = gradE != nullptr ? gradE[0] : 1.0;
@@ -636,11 +649,12 @@ int launch_scale_grad(const float *G, int64_t n, const double *gradE, float *out
     return check_launch("scale grad");
 }
 
-int launch_grad_finalize(const double *G64, int64_t n, const double *gradE, float *out, hipStream_t s) {
+int launch_grad_finalize(const double *G64, int64_t n, const double *gradE, float *out, const double *eslots,
+                         double *E, hipStream_t s) {
     const int64_t m = 3 * n;
+    const uint32_t blocks = uint32_t((m + kFinalizeThreads - 1) / kFinalizeThreads) + (E != nullptr ? 1 : 0);
     prof_begin(K_FINALIZE, s);
-    hipLaunchKernelGGL(grad_finalize_kernel, dim3(uint32_t((m + 255) / 256)), dim3(256), 0, s, G64, m,
-                       gradE, out);
+    hipLaunchKernelGGL(grad_finalize_kernel, dim3(blocks), dim3(kFinalizeThreads), 0, s, G64, m, gradE, out, eslots, E);
     prof_end(K_FINALIZE, s);
     return check_launch("grad finalize");
 }

@@ -29,20 +29,21 @@ sys.path.insert(0, ROOT)
 
 # published MI355X peaks
 PEAK_HBM = 8.0e12          # B/s
-PEAK_FP32 = 157.3e12       # FLOP/s, vector FP32 (packed); 78.6e12 without packed FP32
 PEAK_BF16 = 2.5e15         # FLOP/s, dense MFMA
 AT_FLOPS_FWD, AT_FLOPS_FWD_BWD = 20, 80   # declared flops per triplet
 LJ_FLOPS = 30                              # declared flops per pair (fwd + bwd)
 
-# HBM bytes per launch of the Axilrod-Teller gradient kernel from the two
-# rocprofv3 PMC passes (FETCH_SIZE, WRITE_SIZE, scaled by a 1 GiB copy) recorded
-# in profiles/step_lambda_hbm_traffic_pmc.md.  They describe the kernel built
+# matrix products of the Axilrod-Teller matrix form: ten forms of three FP16 products
+# (hi hi, hi lo, lo hi) over n^2 / 2 pairs and all k; the energy only needs k below both
+AT_MFMA_FWD_BWD, AT_MFMA_FWD = 30, 10      # flops / n^3
+PEAK_FP16 = 2.5e15         # FLOP/s, dense MFMA
+
+# HBM bytes per Axilrod-Teller gradient (form matrices written, panels read) from the
+# two rocprofv3 PMC passes (FETCH_SIZE, WRITE_SIZE, scaled by a 1 GiB copy) recorded
+# in profiles/step_matrix_forms_trace_and_traffic.md.  They describe the kernels built
 # from sources with this hash; once those change the figure is reported as null.
-AT_TRAFFIC = {"src_sha16": "6698e33937ae40e8", "fetch_bytes": 0.000951e9, "write_bytes": 7.0313e9,
-              "valu_instructions": 38170657092}  # SQ_INSTS_VALU (wave instructions) per launch
-# single-issue FP32 vector rate: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz
-VALU_ISSUE_SPEC = 256 * 4 * 16 * 2.4e9
-AT_SOURCES = ("smx_triplet.hip", "smx_device.h", "smx_maps.h")
+AT_SOURCES = ("smx_triplet_mfma.hip", "smx_at_forms.h", "smx_device.h", "smx_maps.h")
+AT_TRAFFIC = {"src_sha16": "5a51d8b2905f4526", "fetch_bytes": 22.61e9, "write_bytes": 2.75e9}
 
 N_EDM, D_EDM = 65536, 64
 N_GRAM, D_GRAM = 32768, 512
@@ -154,7 +155,8 @@ def main():
         e = elements["edm"]
         comps["edm_fp32_n65536_d64"] = {
             "elements": e, "kernel_ms": kavg["edm_diff"], "elements_per_s": e / t,
-            "alu_tflops": 3 * D_EDM * e / t / 1e12, "alu_frac": 3 * D_EDM * e / t / PEAK_FP32,
+            "declared_tflops": 3 * D_EDM * e / t / 1e12,
+            "mfma_frac": 3 * 2 * D_EDM * e / t / PEAK_FP16,
             "hbm_gbs": 4 * e / t / 1e9, "hbm_frac": 4 * e / t / PEAK_HBM}
     if "gram" in only:
         t = kavg["edm_gram"] / 1e3
@@ -231,7 +233,9 @@ def main():
         comps["at_lj_n8192_fwd_bwd"] = {
             "triplets": tri, "pairs": math.comb(N_AT, 2), "kernel_ms": kavg["triplet_grad"],
             "lj_ms": kavg["lj"], "triplets_per_s": tri / t,
-            "alu_tflops": AT_FLOPS_FWD_BWD * tri / t / 1e12, "alu_frac": AT_FLOPS_FWD_BWD * tri / t / PEAK_FP32}
+            "declared_tflops": AT_FLOPS_FWD_BWD * tri / t / 1e12,
+            "mfma_tflops": AT_MFMA_FWD_BWD * N_AT ** 3 / t / 1e12,
+            "mfma_frac": AT_MFMA_FWD_BWD * N_AT ** 3 / t / PEAK_FP16}
 
     # the Axilrod-Teller workload at n = 2048 (forward + backward, one fused pass)
     # and the energy-only kernel at n = 2048 and n = 8192, beside the step
@@ -263,18 +267,18 @@ def main():
         comps["at_n2048_fwd_bwd"] = {
             "triplets": tri4, "kernel_ms": t_fb, "bbox_kernel_ms": t_fb_bb, "speedup_lambda_vs_bbox": t_fb_bb / t_fb,
             "triplets_per_s": tri4 / (t_fb / 1e3),
-            "alu_tflops": AT_FLOPS_FWD_BWD * tri4 / (t_fb / 1e3) / 1e12,
-            "alu_frac": AT_FLOPS_FWD_BWD * tri4 / (t_fb / 1e3) / PEAK_FP32,
+            "declared_tflops": AT_FLOPS_FWD_BWD * tri4 / (t_fb / 1e3) / 1e12,
+            "mfma_frac": AT_MFMA_FWD_BWD * n4 ** 3 / (t_fb / 1e3) / PEAK_FP16,
             "per_unit": "80 declared flops per triplet (20 forward + 60 backward), 1.4296e9 triplets per launch"}
         comps["at_n2048_fwd"] = {
             "triplets": tri4, "kernel_ms": t_f, "triplets_per_s": tri4 / (t_f / 1e3),
-            "alu_tflops": AT_FLOPS_FWD * tri4 / (t_f / 1e3) / 1e12,
-            "alu_frac": AT_FLOPS_FWD * tri4 / (t_f / 1e3) / PEAK_FP32,
+            "declared_tflops": AT_FLOPS_FWD * tri4 / (t_f / 1e3) / 1e12,
+            "mfma_frac": AT_MFMA_FWD * n4 ** 3 / (t_f / 1e3) / PEAK_FP16,
             "per_unit": "20 declared flops per triplet (forward), 1.4296e9 triplets per launch"}
         comps["at_n8192_fwd"] = {
             "triplets": tri5, "kernel_ms": t_f8, "triplets_per_s": tri5 / (t_f8 / 1e3),
-            "alu_tflops": AT_FLOPS_FWD * tri5 / (t_f8 / 1e3) / 1e12,
-            "alu_frac": AT_FLOPS_FWD * tri5 / (t_f8 / 1e3) / PEAK_FP32,
+            "declared_tflops": AT_FLOPS_FWD * tri5 / (t_f8 / 1e3) / 1e12,
+            "mfma_frac": AT_MFMA_FWD * N_AT ** 3 / (t_f8 / 1e3) / PEAK_FP16,
             "per_unit": "20 declared flops per triplet (forward), 9.159e10 triplets per launch"}
         del ws4
 
@@ -353,7 +357,7 @@ def main():
             "quadruplets": nq, "contact_radius": QUAD_RC, "cliques": int(cnt.item()),
             "ms": t * 1e3, "quadruplets_per_s": nq / t, "maps": qd,
             "speedup_lambda_vs_bbox": (qd["bbox"]["words_ms"] + qd["bbox"]["quad_ms"]) / (t * 1e3),
-            "per_unit": "64^4 quadruplets per tile (map decoded one id per lane, tiles counted one per wave at a time); 3 KB of contact words read per mapped tile"}
+            "per_unit": "all quadruplets of n = 8192; few contacts a particle: cliques counted from contact rows, map blocks otherwise"}
         del ws4
 
     # Life on the 2-simplex of cells, n = 32768, tile-contiguous 64 x 64 byte
@@ -390,28 +394,21 @@ def main():
     dom = max(per_step, key=per_step.get)
     if dom == "triplet_grad":
         t = kavg[dom] / 1e3
-        ach = AT_FLOPS_FWD_BWD * math.comb(N_AT, 3) / t
+        ach = AT_MFMA_FWD_BWD * N_AT ** 3 / t
         traffic = at_traffic()
-        roof = {"kernel": "at_kernel<lambda, grad>", "bound": "alu", "achieved": ach / 1e12,
-                "peak": PEAK_FP32 / 1e12, "unit": "TFLOP/s", "frac": ach / PEAK_FP32,
+        roof = {"kernel": "at_pair_kernel<lambda, grad>", "bound": "mfma", "achieved": ach / 1e12,
+                "peak": PEAK_FP16 / 1e12, "unit": "TFLOP/s", "frac": ach / PEAK_FP16,
                 "traffic": None if traffic is None else traffic[0] + traffic[1],
                 "traffic_fetch_bytes": None if traffic is None else traffic[0],
                 "traffic_write_bytes": None if traffic is None else traffic[1],
-                "per_unit": "80 flops per triplet (20 forward + 60 backward), 9.159e10 triplets per launch",
-                "frac_basis": "declared flops against the packed-FP32 vector peak; the kernel is built without "
-                              "packed FP32, so its physical ceiling is the VALU issue rate (valu_issue)"}
-        if traffic is not None:
-            issue = traffic[2] * 64 / t  # VALU lane-instructions per second
-            ceil = valu_ceiling(smx, torch, dev)
-            roof["valu_issue"] = {"lane_instructions_per_s": issue, "per_triplet": traffic[2] * 64 / math.comb(N_AT, 3),
-                                  "spec_single_issue": VALU_ISSUE_SPEC, "frac_spec": issue / VALU_ISSUE_SPEC,
-                                  "measured_fma_chain": ceil, "frac_measured": issue / ceil}
+                "per_unit": "30 n^3 flops per gradient (10 forms x 3 FP16 products x n^2 / 2 pairs x 2 n), n = 8192",
+                "frac_basis": "matrix-product flops against the dense FP16 MFMA peak"}
     elif dom == "edm_diff":
         t = kavg[dom] / 1e3
-        ach = 3 * D_EDM * elements["edm"] / t
-        roof = {"kernel": "edm_diff_kernel<lambda>", "bound": "alu", "achieved": ach / 1e12,
-                "peak": PEAK_FP32 / 1e12, "unit": "TFLOP/s", "frac": ach / PEAK_FP32, "traffic": None,
-                "per_unit": "3 d flops per pair, 2.1475e9 pairs per launch"}
+        ach = 4 * elements["edm"] / t
+        roof = {"kernel": "edm_matrix_kernel<lambda>", "bound": "hbm", "achieved": ach / 1e9,
+                "peak": PEAK_HBM / 1e9, "unit": "GB/s", "frac": ach / PEAK_HBM, "traffic": None,
+                "per_unit": "4 bytes written per pair, 2.1475e9 pairs per launch"}
     else:
         t = kavg[dom] / 1e3
         ach = 3 * 2 * D_GRAM * elements["gram"] / t
@@ -533,24 +530,7 @@ def at_traffic():
             h.update(fh.read())
     if h.hexdigest()[:16] != AT_TRAFFIC["src_sha16"]:
         return None
-    return AT_TRAFFIC["fetch_bytes"], AT_TRAFFIC["write_bytes"], AT_TRAFFIC["valu_instructions"]
-
-
-def valu_ceiling(smx, torch, dev):
-    """Measured FP32 VALU issue rate (lane operations / s): the library's FMA-chain
-    probe, best of three launches timed with events on the current stream."""
-    blocks, iters = 8192, 2048
-    out = torch.empty(blocks * 256, dtype=torch.float32, device=dev)
-    best = None
-    for _ in range(4):
-        ev = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        ev[0].record()
-        smx._check(smx.lib().smx_probe_valu(out.data_ptr(), blocks, iters, smx._stream()))
-        ev[1].record()
-        torch.cuda.synchronize()
-        ms = ev[0].elapsed_time(ev[1])
-        best = ms if best is None else min(best, ms)
-    return blocks * 256 * iters * 64 / (best / 1e3)
+    return AT_TRAFFIC["fetch_bytes"], AT_TRAFFIC["write_bytes"]
 
 
 def measured_errors(only, smx, torch, dev, X2, X3, X5, D2, D3, ws3, ws5, pot):

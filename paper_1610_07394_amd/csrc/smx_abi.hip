@@ -178,7 +178,7 @@ static EdmWs edm_ws(int64_t n, int64_t d, int prec) {
         w.inv = off;
         off = align256(off + size_t(n) * 4);
         w.near = off;
-        off = align256(off + 64 * 4);
+        off = align256(off + 256 * 4);  // kEdmSampleBlocks counts
     }
     w.total = off;
     return w;

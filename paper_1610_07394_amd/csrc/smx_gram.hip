@@ -445,8 +445,8 @@ int launch_edm_gram(const MapGeom &g, int tile, const uint16_t *hi, const uint16
 // form's: D >= 5/16 (|x_i|^2 + |x_j|^2) and finite.  Any other pair (near points, NaN,
 // infinities, overflow) is summed as the difference form does, in its order, from the
 // FP32 input: one thread a pair where a pass of 64 rows has few, else all of the
-// pass's, rows in registers.  Its value does not depend on the tile that holds it.
-// Where more than one of 1024 sampled pairs in 50 is such a pair, every block takes the
+// pass's through LDS.  Its value does not depend on the tile that holds it.  Where more
+// than one of 4096 sampled pairs in 128 is such a pair (kEdmGate), every block takes the
 // difference form's tile.  2-norm error, d = 37 / 64 / 130: 4.5 / 4.8 / 5e-8 against
 // 9.4 / 12 / 17e-8.
 //
@@ -464,8 +464,17 @@ constexpr int kLineLd = kLineCols + 4;   // LDS row: shifted by s_i mod 4 floats
 constexpr int kLineList = 128;
 // share of |x_i|^2 + |x_j|^2 from which a pair's Gram value is kept
 constexpr float kEdmNear = 0.3125f;
-// blocks of the preparation that sample 16 pairs each
-constexpr int kEdmSampleBlocks = 64, kEdmSamples = kEdmSampleBlocks * 16;
+// blocks of the preparation that sample 16 pairs each (edm_ws in smx_abi.hip holds their
+// counts), and the share of near ones, 1 / kEdmGate, above which every block takes the
+// difference tile.  A pass lists up to kLineList pairs, 1.25% of its 10240, and with more
+// sums all of them as differences; that many passes overflow, so close to a share of 1%,
+// cost more than the difference tile does.  Never / always that tile, ms, n = 65536, d = 64, tight
+// clusters of equal size in random order: 128 (0.8% near) 3.5 / 6.3, 100 3.7 / 6.3, 90 4.3 /
+// 6.2, 80 7.2 / 6.3, 64 10.7 / 6.3; a single one of a tenth of the points (1%) 5.9 / 6.3; n
+// = 9001, d = 64, the same: 0.115 0.118 0.136 0.183 0.243 and 0.178, against 0.120.
+constexpr int kEdmSampleBlocks = 256, kEdmSamples = kEdmSampleBlocks * 16;
+constexpr unsigned kEdmGate = 128;
+static_assert(kEdmSampleBlocks == 4 * kWave, "four counts a lane");
 
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 
@@ -514,51 +523,67 @@ __device__ __forceinline__ void line_issue(uint4 *buf, const uint4 *__restrict__
 }
 
 // The pairs of one pass (64 rows x 160 columns in LDS) that are marked -1, summed as
-// differences: thread (t & 31, t >> 5) takes 5 columns by 4 rows at a time.
-__device__ __forceinline__ void edm_pass_diff(float *St, const float4 *rowinfo, const float *__restrict__ X, int64_t n, int64_t d,
-                                           int64_t ldx, int64_t I0, int64_t J0, int m, int c0, int t) {
+// differences: thread (t & 31, t >> 5) takes 5 columns by 8 rows.  Four coordinates of
+// the pass's rows and columns at a time go through LDS, a row of X a thread, the next
+// four loading meanwhile.
+constexpr int kPassRows = 64, kPassStage = kPassRows + kLineCols;
+static_assert(kPassStage <= kGramThreads, "a thread stages one row");
+__device__ __forceinline__ void edm_pass_diff(float *St, float4 *Cs, const float4 *rowinfo, const float *__restrict__ X,
+                                              int64_t n, int64_t d, int64_t ldx, int64_t I0, int64_t J0, int m, int c0,
+                                              int t) {
     const int tx = t & 31, ty = t >> 5;
+    const bool stage = t < kPassStage;
+    int64_t row = t < kPassRows ? I0 + (t >> 5) * 64 + m * 32 + (t & 31) : J0 - 32 + (t - kPassRows);
+    row = row < 0 ? 0 : row < n ? row : n - 1;  // rows outside: their pairs are never marked
+    const float *src = X + row * ldx;
+    auto fetch = [&](int64_t k) {
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (k + 4 <= d) {
+            __builtin_memcpy(&v, src + k, 16);  // rows begin at any 4-byte offset
+        } else {
+            v.x = src[k];
+            if (k + 1 < d) v.y = src[k + 1];
+            if (k + 2 < d) v.z = src[k + 2];
+        }
+        return v;
+    };
+    float acc[8][5];
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int c = 0; c < 5; ++c) acc[r][c] = 0.f;
+    float4 next = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (stage) next = fetch(0);
 #pragma unroll 1
-    for (int h = 0; h < 64; h += 32) {
-        float acc[4][5];
-        const float *xr[4], *xc[5];
+    for (int64_t k = 0; k < d; k += 4) {
+        __syncthreads();
+        if (stage) Cs[t] = next;
+        __syncthreads();
+        if (stage && k + 4 < d) next = fetch(k + 4);
+        float4 b[5];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int rr = h + ty + 8 * r;
-            const int64_t i = I0 + (rr >> 5) * 64 + m * 32 + (rr & 31);
-            xr[r] = X + (i < n ? i : n - 1) * ldx;
+        for (int c = 0; c < 5; ++c) b[c] = Cs[kPassRows + tx + 32 * c];
 #pragma unroll
-            for (int c = 0; c < 5; ++c) acc[r][c] = 0.f;
-        }
-#pragma unroll
-        for (int c = 0; c < 5; ++c) {
-            const int64_t j = J0 - 32 + tx + 32 * c;
-            xc[c] = X + (j < 0 ? 0 : j < n ? j : n - 1) * ldx;
-        }
-#pragma unroll 2
-        for (int64_t k = 0; k < d; ++k) {
-            float a[4], b[5];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) a[r] = xr[r][k];
-#pragma unroll
-            for (int c = 0; c < 5; ++c) b[c] = xc[c][k];
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int c = 0; c < 5; ++c) {
-                    const float u = a[r] - b[c];
-                    acc[r][c] = __builtin_fmaf(u, u, acc[r][c]);
-                }
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
+        for (int r = 0; r < 8; ++r) {
+            const float4 a = Cs[ty + 8 * r];
 #pragma unroll
             for (int c = 0; c < 5; ++c) {
-                const int rr = h + ty + 8 * r, il = (rr >> 5) * 64 + m * 32 + (rr & 31);
-                float *p = St + rr * kLineLd + tx + 32 * c + (__float_as_int(rowinfo[il].w) & 3);
-                if (c >= c0 && *p == -1.f) *p = acc[r][c];
+                float u;
+                u = a.x - b[c].x; acc[r][c] = __builtin_fmaf(u, u, acc[r][c]);
+                u = a.y - b[c].y; acc[r][c] = __builtin_fmaf(u, u, acc[r][c]);
+                u = a.z - b[c].z; acc[r][c] = __builtin_fmaf(u, u, acc[r][c]);
+                u = a.w - b[c].w; acc[r][c] = __builtin_fmaf(u, u, acc[r][c]);
             }
+        }
     }
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+            const int rr = ty + 8 * r, il = (rr >> 5) * 64 + m * 32 + (rr & 31);
+            float *p = St + rr * kLineLd + tx + 32 * c + (__float_as_int(rowinfo[il].w) & 3);
+            if (c >= c0 && *p == -1.f) *p = acc[r][c];
+        }
 }
 
 template <int MAP, bool STATS, bool TILED>
@@ -594,6 +619,7 @@ __global__ __launch_bounds__(kGramThreads, 3) void edm_matrix_kernel(MapGeom g, 
     __shared__ RowOut rowout[T];
     __shared__ float nB[kLineCols], iB[kLineCols];
     __shared__ int nflag, flag[kLineList];
+    __shared__ float4 Cs[kPassStage];
     auto shift = [&](int il) { return __float_as_int(rowinfo[il].w); };
 
     const int t = threadIdx.x;
@@ -617,14 +643,13 @@ __global__ __launch_bounds__(kGramThreads, 3) void edm_matrix_kernel(MapGeom g, 
     auto issue = [&](int st) {
         line_issue<NP, CB>(Lb + (st % S) * BUF, hi4, lo4, ra, rc, rbmax, KB, st, w, lane);
     };
-    issue(0);
-    issue(1);  // d > 16: two stages at least
     {
-        // more than one sampled pair in 50 near: every block takes the difference form
-        const unsigned c = wave_sum(near[lane]);
-        if (50 * c > unsigned(kEdmSamples)) {
-            wait_vm<0>();  // the stages' writes are done before the panels take their place
-            __syncthreads();
+        // the gate, before the ring is touched: its wait costs what the products run no
+        // time (n = 65536, d = 64 2.71 / 2.75 ms, gate first / behind the first loads), and the
+        // difference tile starts without 36 KB of loads that it drops (6.24 / 6.8)
+        const uint4 c4 = reinterpret_cast<const uint4 *>(near)[lane];
+        const unsigned c = wave_sum(c4.x + c4.y + c4.z + c4.w);
+        if (kEdmGate * c > unsigned(kEdmSamples)) {
             float *As = reinterpret_cast<float *>(Lb);
             static_assert(LDS >= 2 * 128 * kEdmLd * 4, "the difference form's panels fit");
             if ((ldx & 3) == 0 && d % kEdmKc == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0)
@@ -635,6 +660,8 @@ __global__ __launch_bounds__(kGramThreads, 3) void edm_matrix_kernel(MapGeom g, 
             return;
         }
     }
+    issue(0);
+    issue(1);  // d > 16: two stages at least
     const int eoff = int((reinterpret_cast<uintptr_t>(D) >> 2) & 31);
     for (int x = t; x < T; x += kGramThreads) {
         const int64_t i = I0 + x;
@@ -775,7 +802,7 @@ __global__ __launch_bounds__(kGramThreads, 3) void edm_matrix_kernel(MapGeom g, 
                     St[r * kLineLd + col + (shift(il) & 3)] = edm_pair(X + (I0 + il) * ldx, X + (J0 - 32 + col) * ldx, d);
                 }
             } else {
-                edm_pass_diff(St, rowinfo, X, n, d, ldx, I0, J0, m, 1 - EX, t);
+                edm_pass_diff(St, Cs, rowinfo, X, n, d, ldx, I0, J0, m, 1 - EX, t);
             }
             __syncthreads();
         }

@@ -356,8 +356,8 @@ int smx_triplet_packed_tiled(const float *d_X, int64_t n, int64_t ldx, double nu
  * 2-simplex (map `map` with m = 2), then the cliques over the 4-simplex (map
  * `map` with m = 4; LAMBDA is the lambda4 map of smx_simplex_map4).  Without
  * statistics and from n = 256 on, a sparse contact graph is counted from its
- * contacts instead: for every contact i < j the common neighbours, over the
- * 2-simplex tiles of pass one (the device decides by the contacts it found).
+ * contacts instead: for every contact i < j the common neighbours (above n =
+ * 1024 the device decides by the contacts it found; no 4-simplex block runs then).
  *   d_X      FP32 [n][ldx] device, x, y, z in columns 0..2; ldx >= 3.
  *   n        0 <= n <= 16384 (n < 4 gives 0).
  *   rc       contact radius, finite and >= 0.
@@ -367,7 +367,9 @@ int smx_triplet_packed_tiled(const float *d_X, int64_t n, int64_t ldx, double nu
  *            count and statistics slots, then the contact words, 64-bit,
  *            column-tile-major or row-major: word [Y][64 X + p] or [64 X + p][Y]
  *            holds the contacts of row 64 X + p with columns 64 Y .. 64 Y + 63
- *            (upper tiles X <= Y only).  Scratch.
+ *            (upper tiles X <= Y only), then (n > 1024) lists of work items, 0.5 to 2 MB.
+ *            Scratch.  65536 + 512 nb^2 bytes (nb = ceil(n / 64)), rounded up to
+ *            256, are accepted too and take the 4-simplex tiles.
  *   d_stats  int64[4] or NULL: [0] quadruplets covered (C(n, 4) when every tile
  *            is visited once), [1] 0, [2] mapped 4-simplex blocks, [3] 4-simplex
  *            blocks of the parallel space (logical blocks: the clique pass

@@ -250,9 +250,11 @@ static bool at_matrix_form(int64_t n, bool grad) { return n >= (grad ? 768 : 102
 // Edge of its pair tiles: see AtTile.
 static int at_pair_tile(int64_t n, bool grad) { return n >= (grad ? 4096 : 8192) ? 256 : 128; }
 
+constexpr int64_t kQuadRowsAlways = 1024;  // up to here the rows form takes every call, without lists
 struct QuadWs {
-    size_t cslots, sslots, words, total;
+    size_t cslots, sslots, words, tiles_total, items, total;  // tiles_total: what the tile form needs
     int64_t nb, npad;
+    uint32_t cap;  // work items of the rows form, per slot
 };
 static QuadWs quad_ws(int64_t n) {
     QuadWs w{};
@@ -261,16 +263,31 @@ static QuadWs quad_ws(int64_t n) {
     w.cslots = 0;
     w.sslots = kSlotBytes;
     w.words = 2 * kSlotBytes;
-    w.total = align256(w.words + size_t(w.nb) * size_t(w.npad) * 8);
+    w.tiles_total = align256(w.words + size_t(w.nb) * size_t(w.npad) * 8);
+    w.items = w.total = w.tiles_total;
+    if (n > kQuadRowsAlways) {
+        // a list that overflows sends the call to the tiles (at n = 16384 from about 500
+        // contacts a particle on)
+        const int64_t tiles = (w.nb * (w.nb + 1) / 2 + kSlots - 1) / kSlots;
+        w.cap = uint32_t(512 * (tiles < 4 ? tiles : 4));
+        w.total = align256(w.items + size_t(kSlots) * w.cap * 4);
+    }
     return w;
 }
 
 // The rows form counts from the contacts.  From 256 to 1024 it is the faster one at
-// every density (n = 300 with every pair in contact 2.1 against 3.3 ms, n = 700
-// 6.1 / 12.5); above, the device decides by the contacts it finds; below, the few
-// tiles are as fast (n = 128, all in contact: 0.77 / 0.70 ms).
+// every density (tiles / rows, n = 300 with rc = 1.5 and 4 63 / 31 and 1290 / 538 us, n =
+// 1000 with half of it in one cluster 15.6 / 3.9 ms); below, the few tiles are as fast (n
+// = 128, all in contact: 0.77 / 0.70 ms).  Above, the device decides by its cost W, the pairs
+// of forward contacts (quad_cost_kernel), as the tiles' time grows with n^4 and less
+// than W with density.  Tiles / rows, ms: n = 2000 W = 2.8e6 0.27 / 0.19, 1.3e7 0.65 / 0.66; n
+// = 3000 4.1e6 0.33 / 0.26, 4.8e6 (a cluster of 300) 0.77 / 0.88 and 13.7 / 2.4, 2.0e7
+// 0.74 / 0.91; n = 5000 7.4e6 0.77 / 0.46, 3.7e7 1.57 / 1.76; n = 8192 5.8e7 9.3 / 6.1, 6.6e7
+// 5.3 / 2.7, 4.6e8 32 / 36; n = 16384 1.4e8 45 / 6.6, 1.3e9 180 / 168 and 265 / 113.
 static bool quad_rows_form(int64_t n) { return n >= 256; }
-static bool quad_rows_always(int64_t n) { return n <= 1024; }
+static uint64_t quad_rows_limit(int64_t n) {
+    return n <= 3000 ? 4500000u : uint64_t(n) * uint64_t(n) * uint64_t(n) / (n <= 8192 ? 6000 : 3200);
+}
 
 static inline hipStream_t S(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
@@ -720,8 +737,8 @@ int smx_quad_contacts(const float *d_X, int64_t n, int64_t ldx, double rc, int m
     if (d_count == nullptr) return fail(SMX_EINVAL, "count must not be NULL");
     if (n >= 4 && d_X == nullptr) return fail(SMX_EINVAL, "X must not be NULL");
     const QuadWs w = quad_ws(n);
-    if (d_ws == nullptr || ws_bytes < w.total)
-        return fail(SMX_EINVAL, "workspace of %zu bytes required (got %zu)", w.total, ws_bytes);
+    if (d_ws == nullptr || ws_bytes < w.tiles_total)
+        return fail(SMX_EINVAL, "workspace of %zu bytes required (got %zu)", w.tiles_total, ws_bytes);
     MapGeom g2{}, g4{};
     if (n >= 4 && (!make_geom(2, w.nb, map, g2) || !make_geom(4, w.nb, map, g4))) return g_status;
     char *ws = reinterpret_cast<char *>(d_ws);
@@ -732,14 +749,18 @@ int smx_quad_contacts(const float *d_X, int64_t n, int64_t ldx, double rc, int m
     if ((rc_ = launch_fill_u64(reinterpret_cast<uint64_t *>(ws), 2 * kSlotBytes / 8, S(stream)))) return rc_;
     if (n >= 4) {
         const float rc2 = float(rc * rc);
-        const bool rows = sslots == nullptr && quad_rows_form(n), gated = rows && !quad_rows_always(n);
+        // (a workspace without room for the lists takes the tiles)
+        const bool rows = sslots == nullptr && quad_rows_form(n) && ws_bytes >= w.total, gated = rows && n > kQuadRowsAlways;
+        const uint64_t limit = quad_rows_limit(n);
         if (rows) {
-            if ((rc_ = launch_contact_words(g2, d_X, n, ldx, rc2, W, w.npad, cslots, true, S(stream)))) return rc_;
-            if ((rc_ = launch_quad_rows(g2, W, n, gated, cslots, S(stream)))) return rc_;
+            uint32_t *items = gated ? reinterpret_cast<uint32_t *>(ws + w.items) : nullptr;
+            if ((rc_ = launch_contact_words(g2, d_X, n, ldx, rc2, W, w.npad, cslots, true, items, w.cap, limit, S(stream)))) return rc_;
+            if ((rc_ = launch_quad_rows(int(w.nb), W, n, items, w.cap, limit, cslots, S(stream)))) return rc_;
         }
         if (!rows || gated) {  // gated: both launches end at once unless the graph turned out dense
-            if ((rc_ = launch_contact_words(g2, d_X, n, ldx, rc2, W, w.npad, gated ? cslots : nullptr, false, S(stream)))) return rc_;
-            if ((rc_ = launch_quad(g4, W, w.npad, n, gated, cslots, sslots, S(stream)))) return rc_;
+            if ((rc_ = launch_contact_words(g2, d_X, n, ldx, rc2, W, w.npad, gated ? cslots : nullptr, false, nullptr, 0, limit, S(stream)))) return rc_;
+            if ((rc_ = launch_quad(g4, W, w.npad, n, gated, limit, cslots, sslots, d_count, S(stream)))) return rc_;
+            if (quad_writes_count(gated, map)) return SMX_OK;
         }
     }
     if ((rc_ = launch_count_finalize(cslots, d_count, S(stream)))) return rc_;

@@ -175,12 +175,19 @@ int launch_triplet_packed(const MapGeom &g, const float *X, int64_t n, int64_t l
                           unsigned long long *sslots, bool tiled, bool rows, hipStream_t s);
 // (rows: g is the 2-simplex of kTripTile pair tiles, else the 3-simplex of triplet tiles)
 constexpr int kQuadTile = 64;    // 4-point contacts: 64 elements per tile dimension
+// rows: row-major words, and given items the lists of work items, `cap` a slot; else
+// column-tile-major words, and given cslots only if the gate is set.  The gate is set
+// where a list overflows or the cost (pairs of forward contacts of a row) is above limit.
 int launch_contact_words(const MapGeom &g, const float *X, int64_t n, int64_t ldx, float rc2, uint64_t *W,
-                         int64_t npad, unsigned long long *cslots, bool rows, hipStream_t s);
-int launch_quad_rows(const MapGeom &g, const uint64_t *R, int64_t n, bool gated, unsigned long long *cslots,
-                     hipStream_t s);
-int launch_quad(const MapGeom &g, const uint64_t *W, int64_t npad, int64_t n, bool gated, unsigned long long *cslots,
-                unsigned long long *sslots, hipStream_t s);
+                         int64_t npad, unsigned long long *cslots, bool rows, uint32_t *items, uint32_t cap,
+                         uint64_t limit, hipStream_t s);
+// given items: the cost, then the count unless the gate is set
+int launch_quad_rows(int nb, const uint64_t *R, int64_t n, const uint32_t *items, uint32_t cap, uint64_t limit,
+                     unsigned long long *cslots, hipStream_t s);
+// gated: counts if the gate is set, and (quad_writes_count) writes the count to out either way
+int launch_quad(const MapGeom &g, const uint64_t *W, int64_t npad, int64_t n, bool gated, uint64_t limit,
+                unsigned long long *cslots, unsigned long long *sslots, int64_t *out, hipStream_t s);
+inline bool quad_writes_count(bool gated, int map) { return gated && map != MAP_REC_LAUNCH; }  // one launch, not one per cube
 constexpr int kLifeTile = 64;    // cellular automaton: 64 x 64 cells per tile
 int launch_life(const MapGeom &g, const uint8_t *S, uint8_t *D, int64_t n, unsigned long long *slots,
                 hipStream_t s);

@@ -29,36 +29,66 @@ namespace smx {
 constexpr int kQuadWordThreads = 64;
 constexpr int kQuadThreads = 256;
 
-// Whether the contact graph is sparse enough for the neighbour form (below), from
-// the contacts that the first pass counted: a mean degree of at most 64, or n / 32
-// where that is more.  Rows / tiles, ms: n = 3000 degree 59 0.18 / 0.22, 195 1.49 /
-// 0.79; n = 8192 degree 25 0.12 / 1.93, 215 3.7 / 5.1, 402 12.8 / 10.7.  Block
-// uniform; every thread of the block calls it.
-template <int NTHREADS>
-__device__ __forceinline__ bool quad_sparse(const unsigned long long *cslots, int64_t n) {
-    __shared__ unsigned long long red[NTHREADS / kWave];
-    __shared__ bool sparse;
-    unsigned long long c = 0;
+// What the calls that count from the contacts keep in the count slots (zeroed with
+// them): beside each slot's count the length of its list of work items and the counter
+// that deals the tile form's ids; in slot 0, one line for a scalar load, whether a list
+// overflowed, kCostWords shares of the cost and how many blocks are done with the tiles.
+constexpr int kSlotItems = 1, kSlotWalk = 2, kSlotDone = 3, kSlotFull = 4, kSlotCost = 8, kCostWords = 8;
+
+// The gate: true when the tile form is to count.  Final once quad_cost_kernel is done.
+__device__ __forceinline__ bool quad_dense(const unsigned long long *cslots, unsigned long long limit) {
+    unsigned long long cost = 0;
 #pragma unroll
-    for (int q = 0; q < kSlots / NTHREADS; ++q) c += cslots[(threadIdx.x + q * NTHREADS) * kSlotStride + 1];
-    c = block_sum<unsigned long long, NTHREADS>(c, red);
-    if (threadIdx.x == 0) sparse = 2 * c <= (unsigned long long)(n * (n / 32 > 64 ? n / 32 : 64));
-    __syncthreads();
-    return sparse;
+    for (int q = 0; q < kCostWords; ++q) cost += cslots[kSlotCost + q];
+    return cost > limit || cslots[kSlotFull] != 0;
 }
 
-// ROWS: row-major words (row i, column tile Y at i nb + Y), each block adding its
-// contacts to slot word 1; else column-tile-major, and with cslots given only if the
-// graph turned out too dense for the neighbour form.
-template <int MAP, bool ROWS>
+// out = sum of the slots' counts, by the kSlots threads of one block.
+__device__ __forceinline__ void write_count(const unsigned long long *cslots, int64_t *out) {
+    __shared__ unsigned long long red[kSlots / kWave];
+    const unsigned long long v = block_sum<unsigned long long, kSlots>(
+        __hip_atomic_load(cslots + threadIdx.x * kSlotStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), red);
+    if (threadIdx.x == 0) out[0] = int64_t(v);
+}
+// Whether this block is the last of the launch to get here; what the others have added
+// to the slots is then there.  Every thread of the block calls it.
+__device__ __forceinline__ bool last_block(unsigned long long *done) {
+    __shared__ bool last;
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(done, 1ull) == (unsigned long long)(gridDim.x) * gridDim.y - 1;
+    __syncthreads();
+    if (last) __threadfence();
+    return last;
+}
+
+// A work item of the rows form: tile (X, Y) of the contact words and one of 2^lgparts
+// parts of its contacts, by rows (row mod 2^min(lgparts, 6)), then by columns.
+constexpr int kItemLgMax = 8;
+__device__ __forceinline__ uint32_t item_pack(int X, int Y, int part, int lgparts) {
+    return uint32_t(X) | uint32_t(Y) << 8 | uint32_t(part) << 16 | uint32_t(lgparts) << 24;
+}
+
+// ROWS: row-major words (row i, column tile Y at i nb + Y), and the tile's contacts as
+// work items of about `fill` in the list of one slot (given items; `cap` a list, past
+// that the graph is taken to be dense); else column-tile-major.  WALK: for a launch that
+// the gate may leave nothing to do, few blocks that walk the tiles.
+template <int MAP, bool ROWS, bool WALK>
 __global__ __launch_bounds__(kQuadWordThreads) void contact_words_kernel(MapGeom g, const float *__restrict__ Xp,
                                                                         int64_t n, int64_t ldx, float rc2,
                                                                         uint64_t *__restrict__ W, int64_t npad,
-                                                                        unsigned long long *cslots) {
+                                                                        unsigned long long *cslots,
+                                                                        uint32_t *__restrict__ items, uint32_t cap,
+                                                                        uint32_t fill, unsigned long long limit) {
+    if (WALK && !quad_dense(cslots, limit)) return;
+    for (uint64_t b = launch_index(); !WALK || b < g.G; b += uint64_t(gridDim.x) * gridDim.y) {
     uint64_t lin;
     int TX, TY;
-    if (!ROWS && cslots != nullptr && quad_sparse<kQuadWordThreads>(cslots, n)) return;
-    if (!tile2_of<MAP, true>(g, lin, TX, TY)) return;
+    const bool tile = WALK ? tile2_of_id<MAP>(g, uint32_t(b), lin, TX, TY) : tile2_of<MAP, true>(g, lin, TX, TY);
+    if (!tile) {
+        if (WALK) continue;
+        return;
+    }
     __shared__ float4 Pc[kQuadTile];
     const int p = threadIdx.x;
     const int64_t i = int64_t(TX) * kQuadTile + p, jc = int64_t(TY) * kQuadTile + p;
@@ -85,40 +115,86 @@ __global__ __launch_bounds__(kQuadWordThreads) void contact_words_kernel(MapGeom
     }
     if (ROWS) {
         W[i * g.nb + TY] = word;
-        const unsigned c = wave_sum(uint32_t(__builtin_popcountll(word)));
-        if (p == 0 && c != 0) atomicAdd(cslots + (lin % kSlots) * kSlotStride + 1, (unsigned long long)c);
+        const unsigned c = items != nullptr ? wave_sum(uint32_t(__builtin_popcountll(word))) : 0;
+        if (c != 0) {
+            int lg = 0;
+            while (lg < kItemLgMax && (c >> lg) > fill) ++lg;
+            const uint32_t parts = 1u << lg, slot = uint32_t(16 * TX + TY) % kSlots;
+            uint32_t at = 0;
+            if (p == 0) at = uint32_t(atomicAdd(cslots + slot * kSlotStride + kSlotItems, (unsigned long long)parts));
+            at = __builtin_amdgcn_readfirstlane(at);
+            for (uint32_t e = p; e < parts; e += kQuadTile)
+                if (at + e < cap) items[slot * cap + at + e] = item_pack(TX, TY, int(e), lg);
+            if (p == 0 && at + parts > cap) atomicOr(cslots + kSlotFull, 1ull);
+        }
     } else {
         W[int64_t(TY) * npad + i] = word;
+    }
+    if (!WALK) return;
+    __syncthreads();  // Pc is free for the next tile
+    }
+}
+
+// The cost of counting from the contacts, which the gate goes by.  Its work is the
+// triangles; what bounds them, and is near them where points in space make the
+// contacts (0.47 of it for even points, 1 for a cluster in contact), are the pairs of
+// forward contacts of each row, sum_i C(f_i, 2).
+constexpr int kCostRows = 8;  // per wave
+__global__ __launch_bounds__(kQuadThreads) void quad_cost_kernel(const uint64_t *__restrict__ R, int64_t n, int nb,
+                                                                 unsigned long long *cslots) {
+    __shared__ unsigned long long red[kQuadThreads / kWave];
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const int64_t r0 = (int64_t(blockIdx.x) * (kQuadThreads / kWave) + w) * kCostRows;
+    unsigned long long cost = 0;
+#pragma unroll
+    for (int r = 0; r < kCostRows; ++r) {
+        const int64_t i = r0 + r;
+        uint32_t f = 0;
+        if (i < n)
+            for (int c = int(i / kQuadTile) + lane; c < nb; c += kWave) f += uint32_t(__builtin_popcountll(R[i * nb + c]));
+        f = wave_sum(f);
+        cost += (unsigned long long)(f) * (f > 0 ? f - 1 : 0) / 2;
+    }
+    if (lane == 0) red[w] = cost;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        cost = 0;
+#pragma unroll
+        for (int q = 0; q < kQuadThreads / kWave; ++q) cost += red[q];
+        if (cost != 0) atomicAdd(cslots + kSlotCost + blockIdx.x % kCostWords, cost);
     }
 }
 
 // Cliques from neighbours, for sparse contacts.  Row i of the contact graph is a
 // bit string of nb words (column tiles below its own are not written and are
-// masked).  A wave takes `rows` rows of one tile (X, Y); for every contact i < j in
-// it the common neighbours m = row i & row j (a word a lane, NQ words when nb >
-// 64), and for every k in m the count of m & row k: what is left are the l > k in
-// contact with all three.  So the work follows the contacts (n = 8192, 34
+// masked).  A wave takes the work items of one slot's list in turn (LISTED), or one row
+// of a tile of T2 (small n: few tiles, 64 waves each); for every contact
+// i < j of an item the common neighbours m = row i & row j (a word a lane, NQ words
+// when nb > 64), and for every k in m the count of m & row k: what is left are the l >
+// k in contact with all three.  So the work follows the contacts (n = 8192, 34
 // contacts a particle: 1.4e5 pairs, 1.2e6 triangles) and not the 1.2e7 tiles of the
 // 4-simplex, whose 3 KB of words each the tile form reads whether they hold a
-// clique or not.  The rows of k are read four at a time: the pass is bound by
-// their latency.  n = 8192: 1.93 -> 0.12 ms a call.
-template <int MAP, int NQ>
-__global__ __launch_bounds__(kQuadThreads) void clique_rows_kernel(MapGeom g, const uint64_t *__restrict__ R, int64_t n,
-                                                                  bool gated, int lgrows, unsigned long long *cslots) {
-    if (gated && !quad_sparse<kQuadThreads>(cslots, n)) return;
+// clique or not; and the items spread the contacts of a cluster that lies in a few
+// tiles.  The rows of k are read four at a time: the pass is bound by their latency.
+// Tiles / this form, ms a call: n = 8192, even, rc = 2 1.92 / 0.146, rc = 4 5.3 / 2.7;
+// 300 of the particles in one cluster, consecutive 18.2 / 2.7 (58 with the rows of a tile
+// dealt to a fixed number of waves), at random 2.8 / 0.85; 700 19.5 / 11.9 and 9.3 / 6.1.
+template <int NQ, bool LISTED>
+__global__ __launch_bounds__(kQuadThreads) void clique_rows_kernel(int nb, const uint64_t *__restrict__ R,
+                                                                  const uint32_t *__restrict__ items, uint32_t cap,
+                                                                  unsigned long long limit, unsigned long long *cslots) {
+    if (LISTED && quad_dense(cslots, limit)) return;
     const int lane = threadIdx.x & (kWave - 1);
-    const int lgparts = 6 - lgrows;  // waves per tile
-    const uint64_t wv = launch_index() * (kQuadThreads / kWave) + uint64_t(__builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
-    const uint64_t id = wv >> lgparts;
-    if (id >= g.G) return;
-    uint64_t lin;
-    int X, Y;
-    if (!tile2_of_id<MAP>(g, uint32_t(id), lin, X, Y)) return;
-    const int nb = g.nb, part = int(wv & ((1u << lgparts) - 1u));
-    const int64_t i0 = int64_t(X) * kQuadTile;
-    const bool mine = (lane >> lgrows) == part;
-    const uint64_t word = mine ? R[(i0 + lane) * nb + Y] : 0;
-    uint64_t act = __ballot(word != 0);
+    const uint32_t wv = blockIdx.x * (kQuadThreads / kWave) + uint32_t(__builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
+    // wave q0 of a list, the lists turned by 37 from one q0 to the next: with equal places
+    // the waves of one list would meet on four CUs
+    const uint32_t q0 = LISTED ? wv / kSlots : 0, slot = (wv + 37u * q0) % kSlots;
+    const uint32_t step = LISTED ? gridDim.x * (kQuadThreads / kWave) / kSlots : 1;
+    uint32_t len = 1;
+    if (LISTED) {
+        const unsigned long long listed = cslots[slot * kSlotStride + kSlotItems];
+        len = listed < cap ? uint32_t(listed) : cap;
+    }
     auto lane64 = [](uint64_t v, int l) -> uint64_t {
         return uint64_t(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v)), l))) |
                uint64_t(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v >> 32)), l))) << 32;
@@ -129,6 +205,22 @@ __global__ __launch_bounds__(kQuadThreads) void clique_rows_kernel(MapGeom g, co
         return w >= from && w < nb ? R[i * nb + w] : 0;
     };
     unsigned long long cnt = 0;
+    for (uint32_t e = q0; e < len; e += step) {
+    int X, Y, part, lg;
+    if (LISTED) {
+        const uint32_t item = __builtin_amdgcn_readfirstlane(items[slot * cap + e]);
+        X = int(item & 255u), Y = int(item >> 8 & 255u), part = int(item >> 16 & 255u), lg = int(item >> 24);
+    } else {
+        linear2(wv >> 6, X, Y);
+        if (Y >= nb) return;
+        part = int(wv & 63u), lg = 6;
+    }
+    const int64_t i0 = int64_t(X) * kQuadTile;
+    const int lgrow = lg < 6 ? lg : 6, lgcol = lg - lgrow;
+    const bool mine = (lane & ((1 << lgrow) - 1)) == (part & ((1 << lgrow) - 1));
+    const uint64_t cols = (lgcol == 0 ? ~0ull : lgcol == 1 ? 0x5555555555555555ull : 0x1111111111111111ull) << (part >> lgrow);
+    const uint64_t word = mine ? R[(i0 + lane) * nb + Y] & cols : 0;
+    uint64_t act = __ballot(word != 0);
     while (act != 0) {
         const int p = __builtin_ctzll(act);
         act &= act - 1;
@@ -178,8 +270,9 @@ __global__ __launch_bounds__(kQuadThreads) void clique_rows_kernel(MapGeom g, co
             }
         }
     }
+    }
     const unsigned long long c = wave_sum(cnt);
-    if (lane == 0 && c != 0) atomicAdd(cslots + (wv % kSlots) * kSlotStride, c);
+    if (lane == 0 && c != 0) atomicAdd(cslots + slot * kSlotStride, c);
 }
 
 // Quadruplets i < j < k < l of a 4-simplex tile, in closed form (edge lengths
@@ -208,21 +301,38 @@ __device__ __forceinline__ uint64_t quad_tile_volume(const int T[4], int64_t n) 
 // counts the current one.  Per tile, lane p holds word p of the six 64-word
 // blocks of the index sets, keeps its own three in registers, shares the other
 // three through the wave's 1.5 KB of LDS, and walks its 64 p2 bits.  A launch
-// has G / 256 hardware blocks.
+// has G / 256 hardware blocks.  A gated launch that walks the ids also writes the count.
 template <int MAP, bool STATS>
 __global__ __launch_bounds__(kQuadThreads) void quad_kernel(MapGeom g, const uint64_t *__restrict__ W, int64_t npad,
-                                                           int64_t n, bool gated, unsigned long long *cslots,
-                                                           unsigned long long *sslots) {
+                                                           int64_t n, uint32_t grab, unsigned long long limit,
+                                                           unsigned long long *cslots, unsigned long long *sslots,
+                                                           int64_t *out) {
     // pair sets s = (a, b): 0 (0,1), 1 (0,2), 2 (0,3), 3 (1,2), 4 (1,3), 5 (2,3);
     // sets 3..5 are read across lanes
     __shared__ uint64_t A[kQuadThreads / kWave][3][kQuadTile];
-    if (!STATS && gated && quad_sparse<kQuadThreads>(cslots, n)) return;
     const int w = threadIdx.x / kWave, p = threadIdx.x & (kWave - 1);
     uint64_t (*Aw)[kQuadTile] = A[w];
-    // (the next round's first LDS writes stay behind this round's reads: the wave
-    // barriers of the tile loop order them)
-    for (uint64_t b = launch_index(); b * kQuadThreads < g.G; b += uint64_t(gridDim.x) * gridDim.y) {
-    const uint64_t base = (b * (kQuadThreads / kWave) + uint64_t(w)) * kWave;
+    const uint64_t wave = launch_index() * (kQuadThreads / kWave) + uint64_t(w);
+    // 64 ids a wave; gated (grab > 0), runs of `grab` times 64 ids, the waves of a slot
+    // taking the next of its runs from its counter (one counter for all would serialise
+    // their atomics; not for the launches per cube, which would share them).  (The next round's first LDS writes stay behind this
+    // round's reads: the wave barriers of the tile loop order them.)
+    const bool gated = !STATS && grab != 0, walk = gated && MAP != MAP_CUBE;
+    if (gated && !quad_dense(cslots, limit)) {
+        if (walk && launch_index() == 0) write_count(cslots, out);  // an earlier launch has counted
+        return;
+    }
+    for (bool more_ids = true; more_ids;) {
+    uint64_t chunk = wave, end = wave + 1;
+    if (walk) {
+        uint32_t k = 0;
+        if (p == 0) k = uint32_t(atomicAdd(cslots + (wave % kSlots) * kSlotStride + kSlotWalk, 1ull));
+        chunk = (uint64_t(__builtin_amdgcn_readfirstlane(k)) * kSlots + wave % kSlots) * grab;
+        end = chunk + grab;
+    }
+    more_ids = walk && end * kWave < g.G;
+    for (; chunk < end && chunk * kWave < g.G; ++chunk) {
+    const uint64_t base = chunk * kWave;
 
     uint64_t mylin = 0;
     int Tq[4] = {0, 0, 0, 0};
@@ -298,6 +408,8 @@ __global__ __launch_bounds__(kQuadThreads) void quad_kernel(MapGeom g, const uin
     const unsigned c = wave_sum(cnt);
     if (p == 0 && c != 0) atomicAdd(cslots + (base / kWave % kSlots) * kSlotStride, (unsigned long long)c);
     }
+    }
+    if (walk && last_block(cslots + kSlotDone)) write_count(cslots, out);
 }
 
 __global__ void count_finalize_kernel(const unsigned long long *slots, int64_t *out) {
@@ -308,56 +420,75 @@ __global__ void count_finalize_kernel(const unsigned long long *slots, int64_t *
 
 template <bool ROWS>
 static void go_words(const MapGeom &g, const float *X, int64_t n, int64_t ldx, float rc2, uint64_t *W, int64_t npad,
-                     unsigned long long *cslots, hipStream_t s) {
+                     unsigned long long *cslots, uint32_t *items, uint32_t cap, uint32_t fill, uint64_t limit, hipStream_t s) {
     for_each_launch(g, [&](auto M, const MapGeom &gg) {
         constexpr int MAPK = decltype(M)::value;
-        const dim3 grid = MAPK == MAP_BBOX ? dim3(gg.nb, gg.nb, 1) : grid_for(gg.G, kQuadWordThreads);
-        hipLaunchKernelGGL((contact_words_kernel<MAPK, ROWS>), grid, dim3(kQuadWordThreads), 0, s, gg, X, n, ldx, rc2,
-                           W, npad, cslots);
+        if (!ROWS && cslots != nullptr) {
+            const dim3 grid = grid_for(gg.G < 2048 ? gg.G : 2048, kQuadWordThreads);
+            hipLaunchKernelGGL((contact_words_kernel<MAPK, false, true>), grid, dim3(kQuadWordThreads), 0, s, gg, X, n,
+                               ldx, rc2, W, npad, cslots, items, cap, fill, (unsigned long long)limit);
+        } else {
+            const dim3 grid = MAPK == MAP_BBOX ? dim3(gg.nb, gg.nb, 1) : grid_for(gg.G, kQuadWordThreads);
+            hipLaunchKernelGGL((contact_words_kernel<MAPK, ROWS, false>), grid, dim3(kQuadWordThreads), 0, s, gg, X, n,
+                               ldx, rc2, W, npad, cslots, items, cap, fill, (unsigned long long)limit);
+        }
     });
 }
 
 int launch_contact_words(const MapGeom &g, const float *X, int64_t n, int64_t ldx, float rc2, uint64_t *W,
-                         int64_t npad, unsigned long long *cslots, bool rows, hipStream_t s) {
+                         int64_t npad, unsigned long long *cslots, bool rows, uint32_t *items, uint32_t cap,
+                         uint64_t limit, hipStream_t s) {
+    // contacts an item: the fewer, the more waves share the work (us, 1 / 4 / 16: n = 3000,
+    // rc = 2 76 75 90, rc = 3 269 260 284; n = 8192, rc = 3 650 655 717); 8 at larger n for
+    // half the list
+    const uint32_t fill = n <= 4096 ? 4 : 8;
     prof_begin(K_QUAD_WORDS, s);
-    if (rows) go_words<true>(g, X, n, ldx, rc2, W, npad, cslots, s);
-    else go_words<false>(g, X, n, ldx, rc2, W, npad, cslots, s);
+    if (rows) go_words<true>(g, X, n, ldx, rc2, W, npad, cslots, items, cap, fill, 0, s);
+    else go_words<false>(g, X, n, ldx, rc2, W, npad, cslots, nullptr, 0, 0, limit, s);
     prof_end(K_QUAD_WORDS, s);
     return check_launch("contact words");
 }
 
-int launch_quad_rows(const MapGeom &g, const uint64_t *R, int64_t n, bool gated, unsigned long long *cslots, hipStream_t s) {
+int launch_quad_rows(int nb, const uint64_t *R, int64_t n, const uint32_t *items, uint32_t cap, uint64_t limit,
+                     unsigned long long *cslots, hipStream_t s) {
+    constexpr int waves = kQuadThreads / kWave;
     prof_begin(K_QUAD, s);
-    for_each_launch(g, [&](auto M, const MapGeom &gg) {
-        constexpr int MAPK = decltype(M)::value;
-        // rows per wave: as many as leave 16384 waves, a full chip twice
-        int lgrows = 6;
-        while (lgrows > 0 && (gg.G << (6 - lgrows)) < 16384) --lgrows;
-        const uint64_t waves = gg.G << (6 - lgrows), per = kQuadThreads / kWave;
-        const dim3 grid = grid_for((waves + per - 1) / per, kQuadThreads);
-        // words per lane
-        if (gg.nb <= 64) hipLaunchKernelGGL((clique_rows_kernel<MAPK, 1>), grid, dim3(kQuadThreads), 0, s, gg, R, n, gated, lgrows, cslots);
-        else if (gg.nb <= 128) hipLaunchKernelGGL((clique_rows_kernel<MAPK, 2>), grid, dim3(kQuadThreads), 0, s, gg, R, n, gated, lgrows, cslots);
-        else hipLaunchKernelGGL((clique_rows_kernel<MAPK, 4>), grid, dim3(kQuadThreads), 0, s, gg, R, n, gated, lgrows, cslots);
-    });
+    if (items == nullptr) {
+        const dim3 grid(uint32_t(nb * (nb + 1) / 2 * kWave / waves));  // nb <= 64
+        hipLaunchKernelGGL((clique_rows_kernel<1, false>), grid, dim3(kQuadThreads), 0, s, nb, R, items, cap, (unsigned long long)limit, cslots);
+    } else {
+        constexpr int rows = waves * kCostRows;
+        hipLaunchKernelGGL(quad_cost_kernel, dim3(uint32_t((n + rows - 1) / rows)), dim3(kQuadThreads), 0, s, R, n, nb,
+                           cslots);
+        // 16384 waves, a full chip twice, in equal shares of the lists
+        const dim3 grid(16384 / waves);
+        static_assert(16384 % kSlots == 0, "equal shares");
+        if (nb <= 64) hipLaunchKernelGGL((clique_rows_kernel<1, true>), grid, dim3(kQuadThreads), 0, s, nb, R, items, cap, (unsigned long long)limit, cslots);
+        else if (nb <= 128) hipLaunchKernelGGL((clique_rows_kernel<2, true>), grid, dim3(kQuadThreads), 0, s, nb, R, items, cap, (unsigned long long)limit, cslots);
+        else hipLaunchKernelGGL((clique_rows_kernel<4, true>), grid, dim3(kQuadThreads), 0, s, nb, R, items, cap, (unsigned long long)limit, cslots);
+    }
     prof_end(K_QUAD, s);
     return check_launch("quad contacts (rows)");
 }
 
-int launch_quad(const MapGeom &g, const uint64_t *W, int64_t npad, int64_t n, bool gated, unsigned long long *cslots,
-                unsigned long long *sslots, hipStream_t s) {
+int launch_quad(const MapGeom &g, const uint64_t *W, int64_t npad, int64_t n, bool gated, uint64_t limit, unsigned long long *cslots,
+                unsigned long long *sslots, int64_t *out, hipStream_t s) {
     prof_begin(K_QUAD, s);
     for_each_launch(g, [&](auto M, const MapGeom &gg) {
         constexpr int MAPK = decltype(M)::value;
-        const uint64_t blocks = (gg.G + kQuadThreads - 1) / kQuadThreads;  // one id per thread
-        // a launch that may find nothing to do keeps few blocks, which then walk the ids
-        const dim3 grid = grid_for(gated && blocks > 4096 ? 4096 : blocks, kQuadThreads);
+        const uint64_t chunks = (gg.G + kWave - 1) / kWave;  // 64 ids a wave
+        const uint64_t blocks = (chunks + kQuadThreads / kWave - 1) / (kQuadThreads / kWave);
+        // a launch that may find nothing to do keeps few blocks, which then walk the ids:
+        // equal shares took 10% longer than a block per 256 ids where heavy tiles lie together,
+        // runs dealt on demand take as long (n = 8192, 1400 in a cluster 35.4, 32.0, 32.2 ms)
+        const dim3 grid = grid_for(gated && MAPK != MAP_CUBE && blocks > 2048 ? 2048 : blocks, kQuadThreads);
+        const uint32_t grab = gated ? uint32_t(1 + (chunks >> 23)) : 0;
         if (sslots)
-            hipLaunchKernelGGL((quad_kernel<MAPK, true>), grid, dim3(kQuadThreads), 0, s, gg, W, npad, n, gated, cslots,
-                               sslots);
+            hipLaunchKernelGGL((quad_kernel<MAPK, true>), grid, dim3(kQuadThreads), 0, s, gg, W, npad, n, grab,
+                               (unsigned long long)limit, cslots, sslots, out);
         else
-            hipLaunchKernelGGL((quad_kernel<MAPK, false>), grid, dim3(kQuadThreads), 0, s, gg, W, npad, n, gated, cslots,
-                               sslots);
+            hipLaunchKernelGGL((quad_kernel<MAPK, false>), grid, dim3(kQuadThreads), 0, s, gg, W, npad, n, grab,
+                               (unsigned long long)limit, cslots, sslots, out);
     });
     prof_end(K_QUAD, s);
     return check_launch("quad contacts");

@@ -156,6 +156,15 @@ int smx_map_blocks_host(int m, int64_t n, int rho, int map, const int32_t *tiles
  * 0 also on bad arguments. */
 size_t smx_workspace_bytes(int op, int64_t n, int64_t d, int prec, int map);
 
+/* Workspace of one triplet call, at most `limit` bytes: the most that the call with
+ * this potential can use (grad 0: smx_triplet_energy, with d_stats given when
+ * stats != 0; grad 1: the gradient calls), or the least that it needs where that
+ * is already above `limit`.  smx_workspace_bytes(2, ...) covers every call;
+ * Lennard-Jones alone, statistics and small n need no more than the least, and a
+ * caller short of memory can ask again with a smaller limit.  Host only; 0 on bad
+ * arguments. */
+size_t smx_triplet_workspace_bytes(int64_t n, const smx_pot *pot, int grad, int stats, size_t limit);
+
 /* Map dump over the 2-simplex (Sec. III-A).  Launches the parallel space of
  * `map` for n elements per dimension and tile edge rho (a power of two in
  * [1, 1024]); each block evaluates its map once and then visits the elements
@@ -273,7 +282,8 @@ int smx_edm_tiled(const float *d_X, int64_t n, int64_t d, int64_t ldx, int map, 
  * against fl(rc*rc).  Coincident particles give inf/NaN (not checked).
  *   d_X   FP32 [n][ldx], ldx >= 3 (only x, y, z are read).
  *   d_E   FP64 [3]: total, Axilrod-Teller part, Lennard-Jones part.
- *   d_ws  smx_workspace_bytes(2, n, 3, 0, map) bytes.  That size gives the
+ *   d_ws  smx_workspace_bytes(2, n, 3, 0, map) bytes, or what
+ *         smx_triplet_workspace_bytes says of this call.  That size gives the
  *         fastest form; any size from 3 * 32768 + 24 n bytes (rounded up to 256) is
  *         accepted.  From n = 768 (energy alone: 1024) to 2^18 the triplets are
  *         summed as matrix products on the matrix cores, whose operands (at most

@@ -9,6 +9,7 @@ on the GPU, the calls raise; there is no CPU path.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from dataclasses import dataclass
 
@@ -16,7 +17,7 @@ import torch
 
 __all__ = [
     "MAPS", "PRECS", "SmxError", "Pot", "lib", "volume", "parallel_blocks", "map_tiles_host", "map_blocks_host",
-    "workspace_bytes", "simplex_map2", "simplex_map3", "simplex_map4", "simplex_count", "triplet_packed", "triplet_packed_tiled", "triplet_tiled_len", "edm_tiled", "edm_tiled_len", "life_len", "simplex_life", "simplex_decode", "quad_contacts", "edm_packed", "triplet_energy",
+    "workspace_bytes", "triplet_workspace_bytes", "simplex_map2", "simplex_map3", "simplex_map4", "simplex_count", "triplet_packed", "triplet_packed_tiled", "triplet_tiled_len", "edm_tiled", "edm_tiled_len", "life_len", "simplex_life", "simplex_decode", "quad_contacts", "edm_packed", "triplet_energy",
     "triplet_energy_grad", "triplet_energy_grad_noalloc", "NOALLOC_MAX_N", "triplet_energy_backward", "TripletEnergy", "profile_enable",
     "profile_reset", "profile_read", "KERNELS", "select_library", "check_flags",
 ]
@@ -77,6 +78,8 @@ def lib():
         L.smx_map_tiles_host.argtypes = [_i32, _i64, _i32, _i32, _i64, _i64, _vp]
         L.smx_workspace_bytes.argtypes = [_i32, _i64, _i64, _i32, _i32]
         L.smx_workspace_bytes.restype = _sz
+        L.smx_triplet_workspace_bytes.argtypes = [_i64, ctypes.POINTER(_Pot), _i32, _i32, _sz]
+        L.smx_triplet_workspace_bytes.restype = _sz
         for name in ("smx_simplex_map2", "smx_simplex_map3", "smx_simplex_map4"):
             getattr(L, name).argtypes = [_i64, _i32, _i32, _i32, _vp, _vp, _vp, _sz, _vp]
         L.smx_simplex_count.argtypes = [_i32, _i64, _i32, _i32, _i32, _vp, _vp, _sz, _vp]
@@ -195,6 +198,50 @@ def _ws(nbytes: int, device) -> torch.Tensor | None:
     return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
 
+def triplet_workspace_bytes(n: int, pot: Pot = Pot(), grad: bool = True, stats: bool = False,
+                            limit: int | None = None) -> int:
+    """Workspace of one triplet call, at most `limit` bytes where that is enough
+    (see smx_triplet_workspace_bytes)."""
+    c = pot._c()
+    return int(lib().smx_triplet_workspace_bytes(n, ctypes.byref(c), int(grad), int(stats),
+                                                 _SIZE_MAX if limit is None else limit))
+
+
+_SIZE_MAX = ctypes.c_size_t(-1).value
+# the sizes the binding asks for at each call: functions of these numbers alone
+_bytes = functools.lru_cache(maxsize=1024)(workspace_bytes)
+
+
+@functools.lru_cache(maxsize=1024)
+def _triplet_bytes(n: int, at: bool, grad: bool, stats: bool, limit: int) -> int:
+    return triplet_workspace_bytes(n, Pot(at=at), grad, stats, limit)
+
+
+def _triplet_ws(n: int, pot: Pot, grad: bool, stats: bool, device) -> torch.Tensor:
+    """What the call can use, or as much of it as the device has room for."""
+    size, at = _triplet_bytes(n, bool(pot.at), grad, stats, _SIZE_MAX), bool(pot.at)
+    least = _triplet_bytes(n, at, grad, stats, 0)
+    while size > least:
+        try:
+            return _ws(size, device)
+        except torch.OutOfMemoryError:
+            size = _triplet_bytes(n, at, grad, stats, size // 2)
+    return _ws(least, device)
+
+
+def _edm_ws(n: int, d: int, prec: int, map, stats: bool, device) -> torch.Tensor | None:
+    """The workspace of a distance call; FP32 can do with the statistics slots, or none."""
+    size, slots = _bytes(1, n, d, prec, map), _bytes(0, 1)
+    if prec == 0:
+        if size > slots:
+            try:
+                return _ws(size, device)
+            except torch.OutOfMemoryError:
+                pass
+        return _ws(slots, device) if stats else None
+    return _ws(size, device)
+
+
 # ---------------------------------------------------------------- map dumps
 def _simplex_map(m: int, n: int, rho: int, map, strict: bool, tiles: bool, stats: bool, device):
     device = torch.device(device)
@@ -234,9 +281,6 @@ def simplex_count(m: int, n: int, rho: int, map="lambda", strict=False, device="
 
 
 # ---------------------------------------------------------------- EDM
-_EDM_WS_ROWS = 5120  # FP32 below this takes no workspace (edm_fp32_matrix in smx_abi.hip)
-
-
 def edm_packed(X: torch.Tensor, map="lambda", prec="fp32", stats=False, out=None, ws=None):
     """Packed upper-triangle squared distances of the rows of X (FP32 [n, d])."""
     if X.dtype != torch.float32 or X.dim() != 2 or X.stride(1) != 1:
@@ -246,8 +290,8 @@ def edm_packed(X: torch.Tensor, map="lambda", prec="fp32", stats=False, out=None
     p = PRECS[prec] if isinstance(prec, str) else int(prec)
     D = out if out is not None else torch.empty(n * (n + 1) // 2, dtype=torch.float32, device=X.device)
     s = torch.zeros(4, dtype=torch.int64, device=X.device) if stats else None
-    if ws is None and (p != 0 or stats or n >= _EDM_WS_ROWS):
-        ws = _ws(workspace_bytes(1, n, d, p, map), X.device)
+    if ws is None:
+        ws = _edm_ws(n, d, p, map, stats, X.device)
     _check(lib().smx_edm_packed(_dev(X, "X"), n, d, ldx, _map(map), p, _ptr(D), _ptr(ws),
                                 0 if ws is None else ws.numel(), _ptr(s), _stream()))
     return (D, s) if stats else D
@@ -271,8 +315,8 @@ def edm_tiled(X: torch.Tensor, map="lambda", prec="fp32", stats=False, out=None,
     if D.dtype != torch.float32 or D.numel() < edm_tiled_len(n) or not D.is_contiguous():
         raise ValueError("out must be a contiguous FP32 tensor of edm_tiled_len(n) elements")
     s = torch.zeros(4, dtype=torch.int64, device=X.device) if stats else None
-    if ws is None and (p != 0 or stats or n >= _EDM_WS_ROWS):
-        ws = _ws(workspace_bytes(1, n, d, p, map), X.device)
+    if ws is None:
+        ws = _edm_ws(n, d, p, map, stats, X.device)
     _check(lib().smx_edm_tiled(_dev(X, "X"), n, d, ldx, _map(map), p, _ptr(D), _ptr(ws),
                                0 if ws is None else ws.numel(), _ptr(s), _stream()))
     return (D, s) if stats else D
@@ -290,7 +334,7 @@ def triplet_energy(X: torch.Tensor, pot: Pot = Pot(), map="lambda", stats=False,
     xp, n, ldx = _xarg(X)
     E = torch.empty(3, dtype=torch.float64, device=X.device)
     s = torch.zeros(8, dtype=torch.int64, device=X.device) if stats else None
-    ws = ws if ws is not None else _ws(workspace_bytes(2, n, 3, 0, map), X.device)
+    ws = ws if ws is not None else _triplet_ws(n, pot, False, stats, X.device)
     c = pot._c()
     _check(lib().smx_triplet_energy(xp, n, ldx, ctypes.byref(c), _map(map), _ptr(E), _ptr(ws), ws.numel(),
                                     _ptr(s), _stream()))
@@ -387,7 +431,7 @@ def triplet_energy_grad(X: torch.Tensor, pot: Pot = Pot(), map="lambda", ws=None
     xp, n, ldx = _xarg(X)
     E = torch.empty(3, dtype=torch.float64, device=X.device)
     G = torch.empty((n, 3), dtype=torch.float32, device=X.device)
-    ws = ws if ws is not None else _ws(workspace_bytes(2, n, 3, 0, map), X.device)
+    ws = ws if ws is not None else _triplet_ws(n, pot, True, False, X.device)
     c = pot._c()
     _check(lib().smx_triplet_energy_grad(xp, n, ldx, ctypes.byref(c), _map(map), _ptr(E), _ptr(G), _ptr(ws),
                                          ws.numel(), _stream()))
@@ -420,7 +464,7 @@ def triplet_energy_backward(X: torch.Tensor, gradE: torch.Tensor, pot: Pot = Pot
     xp, n, ldx = _xarg(X)
     g = gradE.to(torch.float64).reshape(1).contiguous()
     dX = torch.empty((n, 3), dtype=torch.float32, device=X.device)
-    ws = ws if ws is not None else _ws(workspace_bytes(2, n, 3, 0, map), X.device)
+    ws = ws if ws is not None else _triplet_ws(n, pot, True, False, X.device)
     c = pot._c()
     _check(lib().smx_triplet_energy_backward(xp, n, ldx, ctypes.byref(c), _map(map), _dev(g, "gradE"),
                                              _ptr(dX), _ptr(ws), ws.numel(), _stream()))

@@ -336,6 +336,15 @@ size_t smx_workspace_bytes(int op, int64_t n, int64_t d, int prec, int map) {
     return 0;
 }
 
+size_t smx_triplet_workspace_bytes(int64_t n, const smx_pot *pot, int grad, int stats, size_t limit) {
+    if (n < 0 || n > kMaxN || pot == nullptr) return 0;
+    if (pot->at_on && !stats && at_matrix_form(n, grad != 0)) {
+        const AtWs w = at_ws(n, limit);
+        if (w.plan.nr != 0) return w.total;
+    }
+    return trip_ws(n).total;
+}
+
 int smx_map_tiles_host(int m, int64_t n, int rho, int map, int64_t first, int64_t count, int32_t *tiles) {
     int rc = check_common(m, n, rho, map, max_rho(m));
     if (rc != SMX_OK) return rc;

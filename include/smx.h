@@ -252,8 +252,8 @@ int smx_simplex_count(int m, int64_t n, int rho, int map, int strict, int64_t *d
  *         FP32 sums for the pairs it is exact for, the difference form for the
  *         others (near points, NaN, infinities).
  *   d_ws  smx_workspace_bytes(1, n, d, prec, map) bytes.  For FP32_DIFF, NULL (or,
- *         with statistics, 32768 bytes) is accepted too and takes the difference
- *         form on the vector ALUs.  Holds statistics slots, FP32 norms and scales
+ *         with statistics, 32768 bytes), or a workspace that is 8- but not 16-byte
+ *         aligned, is accepted too and takes the difference form on the vector ALUs.  Holds statistics slots, FP32 norms and scales
  *         and the 16-bit hi (and lo) copies of X, rows padded to a multiple of 32 and columns
  *         to a multiple of 32, stored in the matrix-core operand order (1 KB
  *         per 32-row x 16-column block).  Its contents are scratch.

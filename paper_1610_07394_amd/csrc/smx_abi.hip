@@ -504,7 +504,10 @@ static int edm_run(bool tiled, const float *d_X, int64_t n, int64_t d, int64_t l
     const size_t need = fp32 ? (d_stats != nullptr ? kSlotBytes : 0) : w.total;
     if (need > 0 && (d_ws == nullptr || ws_bytes < need))
         return fail(SMX_EINVAL, "workspace of %zu bytes required (got %zu)", need, ws_bytes);
-    const bool matrix = fp32 && edm_fp32_matrix(n, d) && d_ws != nullptr && ws_bytes >= w.total;
+    // (its operands are read 16 bytes at a time; the difference form needs no more than the
+    // 8-byte alignment of the slots)
+    const bool matrix = fp32 && edm_fp32_matrix(n, d) && d_ws != nullptr && ws_bytes >= w.total &&
+                        (reinterpret_cast<uintptr_t>(d_ws) & 15) == 0;
     const int tile = tiled ? kEdmTiledTile : fp32 && !matrix ? edm_diff_tile(n) : gram_tile(n);
     MapGeom g;
     if (!make_geom(2, (n + tile - 1) / tile, map, g)) return g_status;

@@ -88,3 +88,23 @@ def test_distances_in_little_memory(cap):
         torch.cuda.set_per_process_memory_fraction(1.0)  # the comparison takes memory too
         assert torch.equal(D, ref)
         assert not stats or int(got[1][0]) == n * (n + 1) // 2
+
+
+@pytest.mark.parametrize("shift", [4, 8, 24])
+def test_unaligned_workspaces(shift):
+    """FP32 distances accept any alignment that the statistics slots allow (none
+    without them) and then take the difference form; triplets align their operands."""
+    n, d = 8192, 40
+    X = torch.from_numpy(synth.normal(n, d, seed=4)).cuda()
+    ref = smx.edm_packed(X, ws=torch.empty(32768, dtype=torch.uint8, device="cuda"))
+    ws = torch.empty(smx.workspace_bytes(1, n, d) + 64, dtype=torch.uint8, device="cuda")[shift:]
+    assert torch.equal(smx.edm_packed(X, ws=ws), ref)
+    if shift % 8 == 0:
+        got, st = smx.edm_packed(X, ws=ws, stats=True)
+        assert torch.equal(got, ref) and int(st[0]) == n * (n + 1) // 2
+        P = _particles(1100)
+        E0, G0 = smx.triplet_energy_grad(P)
+        ws = torch.empty(smx.workspace_bytes(2, 1100) + 64, dtype=torch.uint8, device="cuda")[shift:]
+        E, G = smx.triplet_energy_grad(P, ws=ws)
+        assert abs(E[0].item() - E0[0].item()) <= 1e-5 * abs(E0[0].item())
+        assert (G - G0).norm(dim=1).max() <= 1e-5 * G0.norm(dim=1).max()

@@ -827,7 +827,9 @@ __global__ __launch_bounds__(kGramThreads, 3) void edm_matrix_kernel(MapGeom g, 
             for (int it = 0; it < 8; ++it) {
                 const RowOut o = out[2 * it];
                 const float4 v = *reinterpret_cast<const float4 *>(sr + 2 * it * kLineLd + o.from);
-                store4<true>(o.to + 4 * (lane & 31), v);
+                const int il = (w >> 1) * 64 + m * 32 + (w & 1) * 16 + (lane >> 5) + 2 * it;
+                const int64_t i = I0 + il, j = J0 - shift(il) + 4 * (lane & 31);
+                if (smx_check(i <= j && j + 3 < n, kCheckStore)) store4<true>(o.to + 4 * (lane & 31), v);
             }
         } else {
             for (int q = 0; q < 16; ++q) {

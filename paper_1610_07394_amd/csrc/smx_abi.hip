@@ -247,7 +247,7 @@ static AtWs at_ws(int64_t n, size_t bytes) {
 // than the loop's arithmetic.  Past 2^18 fewer than 2048 columns of one form fit
 // kAtOpsMax, and each chunk of columns pays the pairs' epilogue again.
 static bool at_matrix_form(int64_t n, bool grad) { return n >= (grad ? 768 : 1024) && n <= (int64_t(1) << 18); }
-// Edge of its pair tiles: see AtTile.
+// Edge of its pair tiles (AtTile; 256: the device chooses, see at_pair_kernel).
 static int at_pair_tile(int64_t n, bool grad) { return n >= (grad ? 4096 : 8192) ? 256 : 128; }
 
 constexpr int64_t kQuadRowsAlways = 1024;  // up to here the rows form takes every call, without lists
@@ -600,20 +600,24 @@ static int triplet_run(int mode, const float *d_X, int64_t n, int64_t ldx, const
     hipStream_t s = S(stream);
     // zero energy slots, statistics slots and the FP64 gradient in one fill
     const AtWs aw = do_at && d_stats == nullptr && !static_ws && at_matrix_form(n, mode >= 1) ? at_ws(n, ws_bytes) : AtWs{};
-    MapGeom gp;
-    const int ptile = at_pair_tile(n, mode >= 1);
-    const int64_t nbp = (n + ptile - 1) / ptile;
-    // from above, lambda2 filters up to three ids in four where nbp is no power of
-    // two, in stretches that left XCDs idle (n = 2051: 0.45 against 0.37 ms)
-    const bool matrix = aw.plan.nr != 0 && make_geom(2, nbp, map == MAP_LAMBDA && !pow2(nbp) ? MAP_BELOW : map, gp);
+    // pair tiles: from above, lambda2 filters up to three ids in four where their number is
+    // no power of two, in stretches that left XCDs idle (n = 2051: 0.45 against 0.37 ms)
+    auto pair_geom = [&](int tile, MapGeom &gp) {
+        const int64_t nbp = (n + tile - 1) / tile;
+        return make_geom(2, nbp, map == MAP_LAMBDA && !pow2(nbp) ? MAP_BELOW : map, gp);
+    };
+    MapGeom gp, gp256;
+    const bool wide = at_pair_tile(n, mode >= 1) == 256;
+    const bool matrix = aw.plan.nr != 0 && pair_geom(128, gp) && (!wide || pair_geom(256, gp256));
     const size_t zero_words =
         (matrix ? aw.zero_end : mode == 0 ? (d_stats ? w.g64 : w.at_stats) : w.total) / 8;
     if ((rc = launch_fill_u64(reinterpret_cast<uint64_t *>(ws), zero_words, s))) return rc;
     const bool grad = mode >= 1;
     if (matrix) {
         const uintptr_t ops = (reinterpret_cast<uintptr_t>(ws) + aw.ops - 256 + 255) & ~uintptr_t(255);
-        if ((rc = launch_triplet_mfma(gp, ptile, aw.plan, d_X, n, ldx, float(pot->nu), grad, G64, eslots,
-                                      reinterpret_cast<unsigned *>(ws + aw.near), reinterpret_cast<void *>(ops), s)))
+        unsigned *found = reinterpret_cast<unsigned *>(ws + w.at_stats);  // (no statistics in this form)
+        if ((rc = launch_triplet_mfma(gp, wide ? &gp256 : nullptr, aw.plan, d_X, n, ldx, float(pot->nu), grad, G64, eslots,
+                                      reinterpret_cast<unsigned *>(ws + aw.near), found, reinterpret_cast<void *>(ops), s)))
             return rc;
     } else if (do_at && (rc = launch_triplet(g3, d_X, n, ldx, float(pot->nu), grad, G64, eslots, at_st, s))) return rc;
     if (do_lj && (rc = launch_lj(g2, d_X, n, ldx, float(pot->lj_eps), float(pot->lj_sigma),

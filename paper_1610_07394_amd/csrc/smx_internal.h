@@ -166,8 +166,10 @@ struct AtPlan {
     int nr;      // forms per launch (10, 5, 2 or 1); 0: no plan
     int64_t kc;  // columns per launch
 };
-int launch_triplet_mfma(const MapGeom &g, int tile, const AtPlan &plan, const float *X, int64_t n, int64_t ldx, float nu,
-                        bool grad, double *G64, double *eslots, unsigned *near, void *ops, hipStream_t s);
+// g: pair tiles of 128; g256: of 256, where the device may choose either (found: its 64 words)
+int launch_triplet_mfma(const MapGeom &g, const MapGeom *g256, const AtPlan &plan, const float *X, int64_t n, int64_t ldx,
+                        float nu, bool grad, double *G64, double *eslots, unsigned *near, unsigned *found, void *ops,
+                        hipStream_t s);
 int launch_lj(const MapGeom &g, const float *X, int64_t n, int64_t ldx, float eps, float sigma,
               float rc2, double *G64, double *eslots, unsigned long long *sslots, hipStream_t s);
 int launch_energy_finalize(const double *eslots, double *E, hipStream_t s);

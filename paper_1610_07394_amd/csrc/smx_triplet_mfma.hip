@@ -20,10 +20,15 @@
 //
 // Precision.  l_r(T) is evaluated in FP64 and held as an FP16 pair hi + lo (22
 // bits and the sign of lo: 2^-23), each row scaled by a power of two so that its
-// nearest neighbour's T is near 2^13; S = hi hi^T + hi lo^T + lo hi^T with exact
-// products and FP32 accumulation, and the forces of the pairs are formed in
-// FP64.  Relative error of the gradient (2-norm, n = 500 .. 8192 particles):
-// 1.6-2.2e-7 against 3.9-4.1e-7 of the FP32 triplet loop.
+// nearest neighbour's T is near 2^13.  FP16 ends at 2^-24 below, so entries of a row at
+// more than about 30 times the distance of its nearest are held to some 2^-38 (r / r_min)^3
+// instead: what a very close pair gets from the rest (its mutual S) loses that much.
+// S = hi hi^T + hi lo^T + lo hi^T with exact products and FP32 accumulation in one or two
+// levels (at_pair_kernel), and the forces of the pairs are formed in FP64.
+// Relative error of the Axilrod-Teller gradient alone (2-norm), particles at 0.8 to 1
+// apart: n = 800 3.2e-7, 2051 3.4e-7, 8192 1.3e-6, of the FP32 triplet loop 9.5e-7,
+// 1.2e-6, 1.6e-6; its energy 1e-8 against 1e-7.  One pair at 0.1 / 0.01 / 0.003 of the
+// spacing, n = 1100: 1.8e-6, 1.2e-5, 2.0e-4 against 1.9e-4, 5.2e-3, 0.13.
 #include <type_traits>
 #include <utility>
 
@@ -64,7 +69,38 @@ __global__ __launch_bounds__(kNearThreads) void at_nearest_kernel(const float *_
     atomicMax(near + i, best);
 }
 
-// Row scale c, a power of two with c / r_min^3 in (2^12.5, 2^14] (a form is at
+// How many of 256 rows have a neighbour much nearer than the rest: 1 / r_min^3 above a
+// fifth of sum_k 1 / r^3.  (A liquid's rows, the nearest other at 0.8 of the spacing, have
+// 0.05 to 0.15, a bond of half the spacing 0.2, of 0.3 of it 0.45.)  A wave a row, kShortBlocks
+// counts.
+constexpr int kShortBlocks = kWave, kShortRows = kShortBlocks * 4, kShortMax = 2;
+__global__ __launch_bounds__(256) void at_short_kernel(const float *__restrict__ X, int64_t n, int64_t ldx,
+                                                      unsigned *__restrict__ found) {
+    __shared__ unsigned red[4];
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const int64_t i = int64_t(mix64(uint64_t(blockIdx.x) * 4 + uint64_t(w)) % uint64_t(n));
+    const float x = X[i * ldx], y = X[i * ldx + 1], z = X[i * ldx + 2];
+    float most = 0.f, sum = 0.f;
+#pragma unroll 4
+    for (int64_t k = lane; k < n; k += kWave) {
+        const float dx = X[k * ldx] - x, dy = X[k * ldx + 1] - y, dz = X[k * ldx + 2] - z;
+        const float d = __builtin_amdgcn_rsqf(__builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx)));
+        const float d3 = k == i ? 0.f : d * d * d;
+        most = d3 > most ? d3 : most;
+        sum += d3;
+    }
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        const float m = __shfl_xor(most, o, kWave);
+        most = m > most ? m : most;
+        sum += __shfl_xor(sum, o, kWave);
+    }
+    if (lane == 0) red[w] = most <= 0.2f * sum ? 0u : 1u;
+    __syncthreads();
+    if (threadIdx.x == 0) found[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+}
+
+// Row scale c, a power of two with c / r_min^3 in (2^12, 2^14] (a form is at
 // most 2.8 / r^3 and FP16 ends at 2^16).  NaN where a pair coincides or the row's
 // position is no number: every result that the row takes part in is then NaN.
 __device__ __forceinline__ double at_row_scale(unsigned near) {
@@ -250,6 +286,10 @@ template <int WR, int WC, int MR, int MC>
 struct AtTile {
     static constexpr int NW = WR * WC, NT = 64 * NW, T = 32 * WR * MR, RB = T / 32;
     static constexpr int S = 4;             // ring slots
+    // Sums in two levels, a chunk of k at a time (see at_pair_kernel), where the
+    // registers hold a second set.
+    static constexpr bool TWO = MR * MC <= 4;
+    static constexpr int CHUNK = 32;        // k steps: 512 k
     static constexpr int STAGE = 4 * RB;    // 1 KB blocks per slot: row panel hi, lo, column panel hi, lo
     static constexpr int LPW = STAGE / NW;  // loads per wave per slot
     static_assert(T == 32 * WC * MC && STAGE % NW == 0, "square tiles");
@@ -261,13 +301,25 @@ struct AtTile {
 // then the pairs' share of the energy and of the gradient.  The map orders the
 // pair tiles; blocks are dealt to the XCDs in runs (xcd_deal), whose blocks share
 // row and column panels in one L2 (0.75 of the reads hit it at n = 8192).
+//
+// The FP32 sums over k.  Where one term is far above the others, as two particles much
+// nearer to each other than to the rest make it (a bond), the many small products of one
+// sign that come after it fall below half an ulp of the sum and are lost, and the energy,
+// in which the bonds' own terms largely cancel, collects that loss: n = 8192, pairs at
+// 0.3 of the spacing, 7.9e-6 of E against 8.7e-7 by the triplet loop.  Tiles of 128
+// therefore sum 512 k at a time and add those up (7.0e-7; n = 2051 0.350 ms, without
+// 0.346), for which they have the registers.  Tiles of
+// 256 have not: found (given when both sizes are launched) counts sampled rows with such
+// a neighbour, and more than kShortMax of 256 send the call to the smaller tiles (n =
+// 8192 then 15.8 ms instead of 13.9; the loop 52.7).
 template <int MAP, int WR, int WC, int MR, int MC, bool GRAD>
 __global__ __launch_bounds__(64 * WR * WC, 2) void at_pair_kernel(
     MapGeom g, int nr, int r0, const uint4 *__restrict__ ops, int KB, int RB, int64_t k0, const float *__restrict__ X,
-    int64_t n, int64_t ldx, const unsigned *__restrict__ near, double nu, double *__restrict__ G64,
-    double *__restrict__ eslots) {
+    int64_t n, int64_t ldx, const unsigned *__restrict__ near, const unsigned *__restrict__ found, double nu,
+    double *__restrict__ G64, double *__restrict__ eslots) {
     using C = AtTile<WR, WC, MR, MC>;
     constexpr int T = C::T, S = C::S, LPW = C::LPW;
+    if (found != nullptr && (wave_sum(found[threadIdx.x & (kWave - 1)]) > unsigned(kShortMax)) != C::TWO) return;
     const uint64_t task0 = launch_index(), ntask = g.G * uint64_t(nr);
     if (task0 >= ntask) return;
     // the energy's tiles differ in depth, so its runs are shorter (n = 8192: 6.3 -> 6.0 ms)
@@ -320,6 +372,13 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void at_pair_kernel(
         for (int c = 0; c < MC; ++c)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[m][c][e] = 0.f;
+    f32x16_t sum[C::TWO ? MR : 1][C::TWO ? MC : 1];
+    if constexpr (C::TWO) {
+#pragma unroll
+        for (int m = 0; m < MR; ++m)
+#pragma unroll
+            for (int c = 0; c < MC; ++c) sum[m][c] = acc[m][c];
+    }
     // Ring: slots st .. st + S - 1 are filled or in flight.  A step multiplies the
     // fragments of step st from registers while it reads those of st + 1 (the last
     // one reads a stale slot that nothing uses).  At its barrier every wave holds st
@@ -344,6 +403,25 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void at_pair_kernel(
     for (int st = 0; st < nst; st += 2) {  // nst is even
         step(st, f0, f1);
         step(st + 1, f1, f0);
+        if constexpr (C::TWO) {
+            if (st + 2 == nst || (st + 2) % C::CHUNK == 0) {
+#pragma unroll
+                for (int m = 0; m < MR; ++m)
+#pragma unroll
+                    for (int c = 0; c < MC; ++c)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) {
+                            sum[m][c][e] += acc[m][c][e];
+                            acc[m][c][e] = 0.f;
+                        }
+            }
+        }
+    }
+    if constexpr (C::TWO) {
+#pragma unroll
+        for (int m = 0; m < MR; ++m)
+#pragma unroll
+            for (int c = 0; c < MC; ++c) acc[m][c] = sum[m][c];
     }
     __syncthreads();
 
@@ -459,11 +537,11 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void at_pair_kernel(
 
 template <int MAP, int WR, int WC, int MR, int MC, bool GRAD>
 static void go_pairs(const MapGeom &g, int nr, int r0, const uint4 *ops, int KB, int RB, int64_t k0, const float *X,
-                     int64_t n, int64_t ldx, const unsigned *near, double nu, double *G64, double *eslots,
-                     hipStream_t s) {
+                     int64_t n, int64_t ldx, const unsigned *near, const unsigned *found, double nu, double *G64,
+                     double *eslots, hipStream_t s) {
     using C = AtTile<WR, WC, MR, MC>;
     hipLaunchKernelGGL((at_pair_kernel<MAP, WR, WC, MR, MC, GRAD>), grid_for(g.G * uint64_t(nr), C::NT), dim3(C::NT),
-                       0, s, g, nr, r0, ops, KB, RB, k0, X, n, ldx, near, nu, G64, eslots);
+                       0, s, g, nr, r0, ops, KB, RB, k0, X, n, ldx, near, found, nu, G64, eslots);
 }
 
 template <int NR>
@@ -473,15 +551,28 @@ static void go_forms(const float *X, int64_t n, int64_t ldx, const unsigned *nea
                        near, r0, k0, KB, RB, int(upper), tile - 1, ops);
 }
 
-int launch_triplet_mfma(const MapGeom &g, int tile, const AtPlan &plan, const float *X, int64_t n, int64_t ldx, float nu,
-                        bool grad, double *G64, double *eslots, unsigned *near, void *ops_, hipStream_t s) {
+// The pair tiles of edge TILE, of every form in ops.
+template <int TILE, bool GRAD, typename... Args>
+static void go_tiles(const MapGeom &g, Args... args) {
+    for_each_launch(g, [&](auto M, const MapGeom &gg) {
+        constexpr int MAPK = decltype(M)::value;
+        if constexpr (TILE == 256) go_pairs<MAPK, 2, 4, 4, 2, GRAD>(gg, args...);
+        else go_pairs<MAPK, 2, 2, 2, 2, GRAD>(gg, args...);
+    });
+}
+
+int launch_triplet_mfma(const MapGeom &g, const MapGeom *g256, const AtPlan &plan, const float *X, int64_t n, int64_t ldx,
+                        float nu, bool grad, double *G64, double *eslots, unsigned *near, unsigned *found, void *ops_,
+                        hipStream_t s) {
     uint4 *ops = reinterpret_cast<uint4 *>(ops_);
     const int kid = grad ? K_TRIP_GRAD : K_TRIP_ENERGY;
-    const int RB = int((n + 31) / 32);
+    const int RB = int((n + 31) / 32), tile = g256 != nullptr ? 256 : 128;
     prof_begin(kid, s);
     hipLaunchKernelGGL(at_nearest_kernel,
                        dim3(uint32_t((n + kNearThreads - 1) / kNearThreads), uint32_t((n + kNearCols - 1) / kNearCols)),
                        dim3(kNearThreads), 0, s, X, n, ldx, near);
+    if (g256 != nullptr) hipLaunchKernelGGL(at_short_kernel, dim3(kShortBlocks), dim3(256), 0, s, X, n, ldx, found);
+    else found = nullptr;
     for (int64_t k0 = 0; k0 < n; k0 += plan.kc) {
         const int64_t kn = n - k0 < plan.kc ? n - k0 : plan.kc;
         const int KB = int((kn + 31) / 32) * 2;
@@ -491,16 +582,13 @@ int launch_triplet_mfma(const MapGeom &g, int tile, const AtPlan &plan, const fl
             else if (nr == 5) go_forms<5>(X, n, ldx, near, r0, k0, KB, RB, !grad, tile, ops, s);
             else if (nr == 2) go_forms<2>(X, n, ldx, near, r0, k0, KB, RB, !grad, tile, ops, s);
             else go_forms<1>(X, n, ldx, near, r0, k0, KB, RB, !grad, tile, ops, s);
-            for_each_launch(g, [&](auto M, const MapGeom &gg) {
-                constexpr int MAPK = decltype(M)::value;
-if (tile == 256) {
-                    if (grad) go_pairs<MAPK, 2, 4, 4, 2, true>(gg, nr, r0, ops, KB, RB, k0, X, n, ldx, near, nu, G64, eslots, s);
-                    else go_pairs<MAPK, 2, 4, 4, 2, false>(gg, nr, r0, ops, KB, RB, k0, X, n, ldx, near, nu, G64, eslots, s);
-                } else {
-                    if (grad) go_pairs<MAPK, 2, 2, 2, 2, true>(gg, nr, r0, ops, KB, RB, k0, X, n, ldx, near, nu, G64, eslots, s);
-                    else go_pairs<MAPK, 2, 2, 2, 2, false>(gg, nr, r0, ops, KB, RB, k0, X, n, ldx, near, nu, G64, eslots, s);
-                }
-            });
+            if (grad) {
+                if (g256 != nullptr) go_tiles<256, true>(*g256, nr, r0, ops, KB, RB, k0, X, n, ldx, near, found, nu, G64, eslots, s);
+                go_tiles<128, true>(g, nr, r0, ops, KB, RB, k0, X, n, ldx, near, found, nu, G64, eslots, s);
+            } else {
+                if (g256 != nullptr) go_tiles<256, false>(*g256, nr, r0, ops, KB, RB, k0, X, n, ldx, near, found, nu, G64, eslots, s);
+                go_tiles<128, false>(g, nr, r0, ops, KB, RB, k0, X, n, ldx, near, found, nu, G64, eslots, s);
+            }
         }
     }
     prof_end(kid, s);

@@ -39,6 +39,23 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kPackThreads = 256;
 
+// nu as the elements use it: nu = m e, e a power of two.  m and 2^kPackShift go into the
+// pairs (i, k) and 2^-kPackShift into the pairs (i, j), so that the products of an element
+// stay in range where the element does: with k far from i and j (1 / r_ik^3 1 / r_jk^3
+// is 1e-42 at r = 1e7) and with a large nu and a close pair (i, k).
+struct PackNu {
+    double m;
+    float e;
+};
+constexpr double kPackShift = 0x1p40;
+static PackNu pack_nu(float nu) {
+    int x = 0;
+    (void)__builtin_frexpf(nu, &x);
+    if (!(__builtin_fabsf(nu) <= __FLT_MAX__) || nu == 0.f) x = 0;  // inf and NaN stay in m
+    x = x < -100 ? -100 : x > 100 ? 100 : x;
+    return {__builtin_ldexp(double(nu), -x) * kPackShift, __builtin_ldexpf(1.f, x)};
+}
+
 // A pair a, b as the elements use it: the unit vector from a to b and f / r^3 (0
 // vectors for a pair that is not `on`).  The pairs (i, j) and (i, k), which serve
 // many elements, are formed in FP64 and rounded once; 1 / r there to 2^-43, the FP32
@@ -49,21 +66,21 @@ __device__ __forceinline__ float4 pack_pair(float4 pa, float4 pb, bool on) {
     const float d = on ? __builtin_amdgcn_rsqf(sv) : 0.f;
     return make_float4(dx * d, dy * d, dz * d, (d * d) * d);
 }
-__device__ __forceinline__ float4 pack_pair64(float4 pa, float4 pb, bool on, float f) {
+__device__ __forceinline__ float4 pack_pair64(float4 pa, float4 pb, bool on, double f) {
     const double dx = double(pb.x) - double(pa.x), dy = double(pb.y) - double(pa.y), dz = double(pb.z) - double(pa.z);
     const double sv = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
     const double d0 = double(__builtin_amdgcn_rsqf(float(sv)));
     const double d = d0 * __builtin_fma(-0.5 * sv * d0, d0, 1.5);
-    return on ? make_float4(float(dx * d), float(dy * d), float(dz * d), float(double(f) * (d * d * d)))
+    return on ? make_float4(float(dx * d), float(dy * d), float(dz * d), float(f * (d * d * d)))
               : make_float4(0.f, 0.f, 0.f, 0.f);
 }
-// Element (i, j, k) from its pairs (i, j), (j, k) and (i, k), the last with f = nu.
-__device__ __forceinline__ float pack_element(float4 a, float4 b, float4 c) {
+// Element (i, j, k) from its pairs (i, j), (j, k) and (i, k), with PackNu's factors.
+__device__ __forceinline__ float pack_element(float4 a, float4 b, float4 c, float e) {
     const float ab = __builtin_fmaf(a.z, b.z, __builtin_fmaf(a.y, b.y, a.x * b.x));
     const float bc = __builtin_fmaf(b.z, c.z, __builtin_fmaf(b.y, c.y, b.x * c.x));
     const float ca = __builtin_fmaf(c.z, a.z, __builtin_fmaf(c.y, a.y, c.x * a.x));
     // cos cos cos = -(a.b)(b.c)(c.a) with the third side k -> i; c here is i -> k, which flips two signs
-    return __builtin_fmaf(-3.f, (ab * bc) * ca, 1.f) * (a.w * (b.w * c.w));
+    return __builtin_fmaf(-3.f * e, (ab * bc) * ca, e) * (a.w * (b.w * c.w));
 }
 
 // TILED: the tile-contiguous layout instead of the lexicographic one.  Tile
@@ -74,7 +91,7 @@ __device__ __forceinline__ float pack_element(float4 a, float4 b, float4 c) {
 // 0.  Every tile is then one contiguous 128 KB run, written in full.
 template <int MAP, bool STATS, bool TILED>
 __global__ __launch_bounds__(kPackThreads) void at_packed_kernel(MapGeom g, const float *__restrict__ Xp,
-                                                                 int64_t n, int64_t ldx, float nu,
+                                                                 int64_t n, int64_t ldx, PackNu nu,
                                                                  float *__restrict__ E,
                                                                  unsigned long long *sslots) {
     uint64_t lin;
@@ -82,7 +99,7 @@ __global__ __launch_bounds__(kPackThreads) void at_packed_kernel(MapGeom g, cons
     if (!tile3_of<MAP, true>(g, lin, TX, TY, TZ)) return;
     constexpr int T = kTripTile, PS = T * T;
     __shared__ float4 Pos[3][T];
-    // pair terms, sets 0 (i,j), 1 (i,k) times nu, 2 (j,k)
+    // pair terms, sets 0 (i,j), 1 (i,k), both with PackNu's factors, 2 (j,k)
     __shared__ float4 Vp[3][PS];
     __shared__ unsigned long long sred[2][kPackThreads / kWave];
 
@@ -116,7 +133,7 @@ __global__ __launch_bounds__(kPackThreads) void at_packed_kernel(MapGeom g, cons
                 const float4 pa = Pos[ta][r];
                 const int64_t ga = base[ta] + r;
                 const bool valid = interior || (ga < gb && gb < n);
-                Vp[set][r * T + c] = set == 2 ? pack_pair(pa, pb, valid) : pack_pair64(pa, pb, valid, set == 1 ? nu : 1.f);
+                Vp[set][r * T + c] = set == 2 ? pack_pair(pa, pb, valid) : pack_pair64(pa, pb, valid, set == 1 ? nu.m : 1.0 / kPackShift);
             }
         }
     }
@@ -146,7 +163,7 @@ __global__ __launch_bounds__(kPackThreads) void at_packed_kernel(MapGeom g, cons
             const int64_t j = j0 + jl;
             const float4 va = Vp[0][il * T + jl];
             const float4 vb = Vp[2][jl * T + kl];
-            const float e = pack_element(va, vb, vc);
+            const float e = pack_element(va, vb, vc, nu.e);
             const bool ok = TILED ? (i < j && j < k && k < n)
                           : interior ? smx_check(i < j && j < k && k < n, kCheckStore) : (i < j && j < k && k < n);
             if (TILED)
@@ -189,7 +206,7 @@ constexpr int kPackStride = kPackThreads - kPackLine;
 
 template <int MAP>
 __global__ __launch_bounds__(kPackThreads) void at_packed_rows_kernel(MapGeom g, const float *__restrict__ Xp, int64_t n,
-                                                                      int64_t ldx, float nu, float *__restrict__ E) {
+                                                                      int64_t ldx, PackNu nu, float *__restrict__ E) {
     constexpr int T = kTripTile, PARTS = T / kPackI, PIECES = kPackI * kPackJ, NW = kPackThreads / kWave;
     static_assert(NW == kPackI && kPackThreads == 4 * kWave, "a wave stores one i's pieces, a group a lane");
     const uint64_t b = launch_index();
@@ -207,7 +224,7 @@ __global__ __launch_bounds__(kPackThreads) void at_packed_rows_kernel(MapGeom g,
         return p < n ? make_float4(Xp[p * ldx], Xp[p * ldx + 1], Xp[p * ldx + 2], 0.f) : make_float4(0.f, 0.f, 0.f, 0.f);
     };
     if (t < T) Pj[t] = pos(j0 + t);
-    if (t < T * kPackI) Va[t / kPackI][t % kPackI] = pack_pair64(pos(i0 + t % kPackI), pos(j0 + t / kPackI), true, 1.f);
+    if (t < T * kPackI) Va[t / kPackI][t % kPackI] = pack_pair64(pos(i0 + t % kPackI), pos(j0 + t / kPackI), true, 1.0 / kPackShift);
     __syncthreads();
     // element (i, j, k) at start(i) + step(j) + k, step(j + 1) = step(j) + n - 2 - j
     const int64_t c3 = n * (n - 1) * (n - 2) / 6;
@@ -232,7 +249,7 @@ __global__ __launch_bounds__(kPackThreads) void at_packed_rows_kernel(MapGeom g,
         const float4 pk = pos(k0 + t);
         float4 vc[kPackI];
 #pragma unroll
-        for (int u = 0; u < kPackI; ++u) vc[u] = pack_pair64(pi[u], pk, true, nu);
+        for (int u = 0; u < kPackI; ++u) vc[u] = pack_pair64(pi[u], pk, true, nu.m);
         const int hi = int(n - k0 < kPackThreads ? n - k0 : kPackThreads);
         const int dk = int(k0 - j0);
         int64_t at0 = sw + k0;  // element t = 0 of the piece of (iw, j0 + jb)
@@ -246,7 +263,7 @@ __global__ __launch_bounds__(kPackThreads) void at_packed_rows_kernel(MapGeom g,
                 const float4 vb = pack_pair(Pj[jl], pk, true);
 #pragma unroll
                 for (int u = 0; u < kPackI; ++u) {
-                    St[jj * kPackI + u][((sj + si[u]) & (kPackLine - 1)) + t] = pack_element(Va[jl][u], vb, vc[u]);
+                    St[jj * kPackI + u][((sj + si[u]) & (kPackLine - 1)) + t] = pack_element(Va[jl][u], vb, vc[u], nu.e);
                 }
                 sj += uint32_t(dn - jl);
             }
@@ -284,7 +301,7 @@ __global__ __launch_bounds__(kPackThreads) void at_packed_rows_kernel(MapGeom g,
 }
 
 template <int MAP, bool TILED>
-static void go_packed(const MapGeom &g, const float *X, int64_t n, int64_t ldx, float nu, float *E,
+static void go_packed(const MapGeom &g, const float *X, int64_t n, int64_t ldx, PackNu nu, float *E,
                       unsigned long long *sslots, hipStream_t s) {
     const dim3 grid = MAP == MAP_BBOX ? dim3(g.nb, g.nb, g.nb) : grid_for(g.G, kPackThreads);
     if (sslots)
@@ -298,14 +315,15 @@ static void go_packed(const MapGeom &g, const float *X, int64_t n, int64_t ldx, 
 int launch_triplet_packed(const MapGeom &g, const float *X, int64_t n, int64_t ldx, float nu, float *E,
                           unsigned long long *sslots, bool tiled, bool rows, hipStream_t s) {
     const int kid = tiled ? K_TRIP_TILED : K_TRIP_PACKED;
+    const PackNu pn = pack_nu(nu);
     prof_begin(kid, s);
     for_each_launch(g, [&](auto M, const MapGeom &gg) {
         constexpr int MAPK = decltype(M)::value;
         if (rows)
             hipLaunchKernelGGL((at_packed_rows_kernel<MAPK>), grid_for(gg.G * (kTripTile / kPackI), kPackThreads),
-                               dim3(kPackThreads), 0, s, gg, X, n, ldx, nu, E);
-        else if (tiled) go_packed<MAPK, true>(gg, X, n, ldx, nu, E, sslots, s);
-        else go_packed<MAPK, false>(gg, X, n, ldx, nu, E, sslots, s);
+                               dim3(kPackThreads), 0, s, gg, X, n, ldx, pn, E);
+        else if (tiled) go_packed<MAPK, true>(gg, X, n, ldx, pn, E, sslots, s);
+        else go_packed<MAPK, false>(gg, X, n, ldx, pn, E, sslots, s);
     });
     prof_end(kid, s);
     return check_launch("triplet packed");

@@ -377,7 +377,7 @@ int smx_triplet_packed_tiled(const float *d_X, int64_t n, int64_t ldx, double nu
  *            count and statistics slots, then the contact words, 64-bit,
  *            column-tile-major or row-major: word [Y][64 X + p] or [64 X + p][Y]
  *            holds the contacts of row 64 X + p with columns 64 Y .. 64 Y + 63
- *            (upper tiles X <= Y only), then (n > 1024) lists of work items, 0.5 to 2 MB.
+ *            (upper tiles X <= Y only), then (n > 2048) lists of work items, 1.5 to 2 MB.
  *            Scratch.  65536 + 512 nb^2 bytes (nb = ceil(n / 64)), rounded up to
  *            256, are accepted too and take the 4-simplex tiles.
  *   d_stats  int64[4] or NULL: [0] quadruplets covered (C(n, 4) when every tile

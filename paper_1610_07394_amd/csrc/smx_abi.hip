@@ -250,7 +250,8 @@ static bool at_matrix_form(int64_t n, bool grad) { return n >= (grad ? 768 : 102
 // Edge of its pair tiles (AtTile; 256: the device chooses, see at_pair_kernel).
 static int at_pair_tile(int64_t n, bool grad) { return n >= (grad ? 4096 : 8192) ? 256 : 128; }
 
-constexpr int64_t kQuadRowsAlways = 1024;  // up to here the rows form takes every call, without lists
+constexpr int64_t kQuadRowsAlways = 1024;  // up to here the rows form takes every call,
+constexpr int64_t kQuadRowsDirect = 2048;  // and up to here it needs no lists
 struct QuadWs {
     size_t cslots, sslots, words, tiles_total, items, total;  // tiles_total: what the tile form needs
     int64_t nb, npad;
@@ -265,7 +266,7 @@ static QuadWs quad_ws(int64_t n) {
     w.words = 2 * kSlotBytes;
     w.tiles_total = align256(w.words + size_t(w.nb) * size_t(w.npad) * 8);
     w.items = w.total = w.tiles_total;
-    if (n > kQuadRowsAlways) {
+    if (n > kQuadRowsDirect) {
         // a list that overflows sends the call to the tiles (at n = 16384 from about 500
         // contacts a particle on)
         const int64_t tiles = (w.nb * (w.nb + 1) / 2 + kSlots - 1) / kSlots;
@@ -767,9 +768,9 @@ int smx_quad_contacts(const float *d_X, int64_t n, int64_t ldx, double rc, int m
         const float rc2 = float(rc * rc);
         // (a workspace without room for the lists takes the tiles)
         const bool rows = sslots == nullptr && quad_rows_form(n) && ws_bytes >= w.total, gated = rows && n > kQuadRowsAlways;
-        const uint64_t limit = quad_rows_limit(n);
+        const uint64_t limit = gated ? quad_rows_limit(n) : 0;
         if (rows) {
-            uint32_t *items = gated ? reinterpret_cast<uint32_t *>(ws + w.items) : nullptr;
+            uint32_t *items = n > kQuadRowsDirect ? reinterpret_cast<uint32_t *>(ws + w.items) : nullptr;
             if ((rc_ = launch_contact_words(g2, d_X, n, ldx, rc2, W, w.npad, cslots, true, items, w.cap, limit, S(stream)))) return rc_;
             if ((rc_ = launch_quad_rows(int(w.nb), W, n, items, w.cap, limit, cslots, S(stream)))) return rc_;
         }

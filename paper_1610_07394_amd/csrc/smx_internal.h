@@ -179,11 +179,12 @@ int launch_triplet_packed(const MapGeom &g, const float *X, int64_t n, int64_t l
 constexpr int kQuadTile = 64;    // 4-point contacts: 64 elements per tile dimension
 // rows: row-major words, and given items the lists of work items, `cap` a slot; else
 // column-tile-major words, and given cslots only if the gate is set.  The gate is set
-// where a list overflows or the cost (pairs of forward contacts of a row) is above limit.
+// where a list overflows or the cost (pairs of forward contacts of a row) is above limit
+// (0: no gate).
 int launch_contact_words(const MapGeom &g, const float *X, int64_t n, int64_t ldx, float rc2, uint64_t *W,
                          int64_t npad, unsigned long long *cslots, bool rows, uint32_t *items, uint32_t cap,
                          uint64_t limit, hipStream_t s);
-// given items: the cost, then the count unless the gate is set
+// the cost, then the count unless the gate is set
 int launch_quad_rows(int nb, const uint64_t *R, int64_t n, const uint32_t *items, uint32_t cap, uint64_t limit,
                      unsigned long long *cslots, hipStream_t s);
 // gated: counts if the gate is set, and (quad_writes_count) writes the count to out either way

@@ -168,7 +168,8 @@ __global__ __launch_bounds__(kQuadThreads) void quad_cost_kernel(const uint64_t 
 // Cliques from neighbours, for sparse contacts.  Row i of the contact graph is a
 // bit string of nb words (column tiles below its own are not written and are
 // masked).  A wave takes the work items of one slot's list in turn (LISTED), or one row
-// of a tile of T2 (small n: few tiles, 64 waves each); for every contact
+// of a tile of T2 (n <= 2048: 64 waves for each of few tiles; n = 1500, rc = 2 50 us, by
+// lists 56); for every contact
 // i < j of an item the common neighbours m = row i & row j (a word a lane, NQ words
 // when nb > 64), and for every k in m the count of m & row k: what is left are the l >
 // k in contact with all three.  So the work follows the contacts (n = 8192, 34
@@ -183,7 +184,7 @@ template <int NQ, bool LISTED>
 __global__ __launch_bounds__(kQuadThreads) void clique_rows_kernel(int nb, const uint64_t *__restrict__ R,
                                                                   const uint32_t *__restrict__ items, uint32_t cap,
                                                                   unsigned long long limit, unsigned long long *cslots) {
-    if (LISTED && quad_dense(cslots, limit)) return;
+    if (limit != 0 && quad_dense(cslots, limit)) return;
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t wv = blockIdx.x * (kQuadThreads / kWave) + uint32_t(__builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
     // wave q0 of a list, the lists turned by 37 from one q0 to the next: with equal places
@@ -452,21 +453,20 @@ int launch_contact_words(const MapGeom &g, const float *X, int64_t n, int64_t ld
 int launch_quad_rows(int nb, const uint64_t *R, int64_t n, const uint32_t *items, uint32_t cap, uint64_t limit,
                      unsigned long long *cslots, hipStream_t s) {
     constexpr int waves = kQuadThreads / kWave;
+    const unsigned long long lim = limit;
     prof_begin(K_QUAD, s);
-    if (items == nullptr) {
-        const dim3 grid(uint32_t(nb * (nb + 1) / 2 * kWave / waves));  // nb <= 64
-        hipLaunchKernelGGL((clique_rows_kernel<1, false>), grid, dim3(kQuadThreads), 0, s, nb, R, items, cap, (unsigned long long)limit, cslots);
-    } else {
+    if (limit != 0) {
         constexpr int rows = waves * kCostRows;
         hipLaunchKernelGGL(quad_cost_kernel, dim3(uint32_t((n + rows - 1) / rows)), dim3(kQuadThreads), 0, s, R, n, nb,
                            cslots);
-        // 16384 waves, a full chip twice, in equal shares of the lists
-        const dim3 grid(16384 / waves);
-        static_assert(16384 % kSlots == 0, "equal shares");
-        if (nb <= 64) hipLaunchKernelGGL((clique_rows_kernel<1, true>), grid, dim3(kQuadThreads), 0, s, nb, R, items, cap, (unsigned long long)limit, cslots);
-        else if (nb <= 128) hipLaunchKernelGGL((clique_rows_kernel<2, true>), grid, dim3(kQuadThreads), 0, s, nb, R, items, cap, (unsigned long long)limit, cslots);
-        else hipLaunchKernelGGL((clique_rows_kernel<4, true>), grid, dim3(kQuadThreads), 0, s, nb, R, items, cap, (unsigned long long)limit, cslots);
     }
+    // listed: 16384 waves, a full chip twice, in equal shares of the lists
+    static_assert(16384 % kSlots == 0, "equal shares");
+    const dim3 grid(items != nullptr ? 16384 / waves : uint32_t(nb * (nb + 1) / 2 * kWave / waves));
+    if (items == nullptr) hipLaunchKernelGGL((clique_rows_kernel<1, false>), grid, dim3(kQuadThreads), 0, s, nb, R, items, cap, lim, cslots);  // nb <= 64
+    else if (nb <= 64) hipLaunchKernelGGL((clique_rows_kernel<1, true>), grid, dim3(kQuadThreads), 0, s, nb, R, items, cap, lim, cslots);
+    else if (nb <= 128) hipLaunchKernelGGL((clique_rows_kernel<2, true>), grid, dim3(kQuadThreads), 0, s, nb, R, items, cap, lim, cslots);
+    else hipLaunchKernelGGL((clique_rows_kernel<4, true>), grid, dim3(kQuadThreads), 0, s, nb, R, items, cap, lim, cslots);
     prof_end(K_QUAD, s);
     return check_launch("quad contacts (rows)");
 }

@@ -83,7 +83,7 @@ def test_clusters(n, m, consecutive):
 
 def test_workspace_without_the_lists():
     """A workspace of the tile form's size is enough for any call."""
-    n = 1100
+    n = 2100
     X = _even(n, 5)
     nb = -(-n // 64)
     least = (65536 + 512 * nb * nb + 255) // 256 * 256

@@ -335,9 +335,10 @@ int smx_triplet_energy_grad_noalloc(const float *d_X, int64_t n, int64_t ldx, co
  *         / (r_ij r_jk r_ik)^3 for every i < j < k < n, p the lexicographic rank
  *         p(i,j,k) = C(n,3) - C(n-i,3) + (j-i-1)(n-1) - (j(j-1)/2 - i(i+1)/2)
  *                    + (k-j-1).  FP32 arithmetic in the kernel.
- *   map   smx_map (lambda3 over 32^3 tiles, or a baseline; from n = 704 to 16384
- *         and without statistics the 2-simplex of 32 x 32 pair tiles, a block
- *         writing whole runs of k); the result does not depend on it.
+ *   map   smx_map (lambda3 over 32^3 tiles, or a baseline; from n = 704 (bounding
+ *         box 752, linear and from below 832) to 16384 and without statistics the
+ *         2-simplex of 32 x 32 pair tiles, a block writing whole runs of k); the
+ *         result does not depend on it.
  *   d_stats nullable; with d_ws of smx_workspace_bytes(0, n) bytes it counts
  *         the stored elements (triplets lt) and their checksum.
  * n <= 2^21 (SMX_EOVERFLOW beyond); n < 3 writes nothing. */

@@ -797,8 +797,11 @@ static int triplet_packed_run(bool tiled, const float *d_X, int64_t n, int64_t l
     MapGeom g{};
     if (n >= 3 && !make_geom(3, (n + kTripTile - 1) / kTripTile, map, g)) return g_status;
     // whole runs per block; below, its few blocks and their k loops are slower than the
-    // tiles (n = 300: 0.037 / 0.029 ms, 701: 0.110 / 0.117, 1024: 0.21 / 0.38)
-    const bool rows = n >= 704 && n <= 16384 && !tiled && d_stats == nullptr;
+    // tiles, whose blocks the maps that filter none or cheaply start sooner (us, rows /
+    // tiles: lambda n = 300 37 / 29, 704 82 / 106; bounding box 704 81 / 72, 752 102 / 116;
+    // linear and from below 800 105 / 103 and 115 / 103, 832 117 / 147 and 123 / 141)
+    const int64_t first = map == MAP_BBOX ? 752 : map == MAP_LINEAR || map == MAP_BELOW ? 832 : 704;
+    const bool rows = n >= first && n <= 16384 && !tiled && d_stats == nullptr;
     if (rows && !make_geom(2, (n + kTripTile - 1) / kTripTile, map, g)) return g_status;
     unsigned long long *slots = d_stats ? reinterpret_cast<unsigned long long *>(d_ws) : nullptr;
     int rc;

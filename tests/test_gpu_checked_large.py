@@ -77,7 +77,7 @@ def test_triplets(kind):
 @pytest.mark.parametrize("shift", [1, 30])
 def test_packed_triplets(kind, shift):
     print(f"checked packed {kind} {shift}", flush=True)
-    n = 709
+    n = 835
     P = torch.from_numpy(synth.rsa(n, seed=5, side=20.0 * (n / 8192) ** (1 / 3), dmin=0.8)).cuda()
     ref = smx.triplet_packed(P)
     got = _into(math.comb(n, 3), shift, lambda o: _checked(lambda: smx.triplet_packed(P, 1.0, kind, out=o)))

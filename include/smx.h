@@ -59,6 +59,10 @@
  *                     paper argues against): (3^(log2 nb' + 1) - 1) / 2
  *                     launches for m = 3, 2 nb' - 1 for m = 2, all on `stream`
  *                     in depth-first order.
+ *   Where nb is no power of two, LAMBDA calls without statistics list their pair
+ *   tiles from below, as LAMBDA_BELOW does, in FP32 distances and in the matrix
+ *   form of the Axilrod-Teller calls: the same tiles without the filtered blocks.
+ *   With statistics the launch is LAMBDA's own, and so are its block counts.
  *   The map changes only the schedule.  EDM outputs are bit-identical across
  *   maps; energies and gradients agree to rounding (atomic order).
  * - Statistics (d_stats, nullable): int64[4] =
@@ -320,6 +324,9 @@ int smx_triplet_energy_backward(const float *d_X, int64_t n, int64_t ldx, const 
  * per device, on the first call with that device current.
  *   d_X, n, ldx, pot, map, d_E (nullable), d_G  as smx_triplet_energy_grad.
  * n > SMX_NOALLOC_MAX_N returns SMX_EINVAL (use smx_triplet_energy_grad).
+ * The array has no room for the matrix form's operands, so the call walks the
+ * 3-simplex at every n: from n = 768 on smx_triplet_energy_grad with its full
+ * workspace is 1.5 to 3.7 times as fast (n = 8192 52.7 against 13.9 ms).
  * Every call on one GPU shares that GPU's array and clears what must start at
  * zero itself; calls that overlap on one GPU (different streams or threads
  * without ordering between them) race on it and give wrong results. */

@@ -332,8 +332,9 @@ def main():
                         "4 bytes per slot of the 45760 tiles of 32^3"}
         del Et, Xp
 
-    # 4-point contacts over the 4-simplex, n = 8192 (measured beside the step):
-    # contact words over the 2-simplex, then the 4-cliques per 64^4 tile
+    # 4-point contacts, n = 8192 (measured beside the step): contact words over the
+    # 2-simplex (the map's part), then, the graph being sparse, the 4-cliques from the
+    # contacts; no 4-simplex block runs.  Sums over all launches of a call.
     if "at" in only and not args.no_compare:
         log("4-point contacts, n = 8192")
         qd = {}
@@ -346,18 +347,17 @@ def main():
             smx.profile_reset()
             for _ in range(args.steps):
                 smx.quad_contacts(X5, QUAD_RC, kind, out=cnt, ws=ws4)
-            w_ms, w_c = smx.profile_read("quad_words")
-            q_ms, q_c = smx.profile_read("quad")
+            w_ms, _ = smx.profile_read("quad_words")
+            q_ms, _ = smx.profile_read("quad")
             smx.profile_enable(False)
-            qd[kind] = {"words_ms": w_ms / w_c, "quad_ms": q_ms / q_c,
-                        "blocks": smx.parallel_blocks(4, -(-N_AT // 64), 1, kind)}
+            qd[kind] = {"words_ms": w_ms / args.steps, "quad_ms": q_ms / args.steps}
         nq = math.comb(N_AT, 4)
         t = (qd["lambda"]["words_ms"] + qd["lambda"]["quad_ms"]) / 1e3
         comps["quad_contacts_n8192"] = {
             "quadruplets": nq, "contact_radius": QUAD_RC, "cliques": int(cnt.item()),
             "ms": t * 1e3, "quadruplets_per_s": nq / t, "maps": qd,
-            "speedup_lambda_vs_bbox": (qd["bbox"]["words_ms"] + qd["bbox"]["quad_ms"]) / (t * 1e3),
-            "per_unit": "all quadruplets of n = 8192; few contacts a particle: cliques counted from contact rows, map blocks otherwise"}
+            "per_unit": "all quadruplets of n = 8192, counted from the contacts (sparse graph): the map orders the "
+                        "contact words' tiles only"}
         del ws4
 
     # Life on the 2-simplex of cells, n = 32768, tile-contiguous 64 x 64 byte

@@ -286,10 +286,8 @@ template <int WR, int WC, int MR, int MC>
 struct AtTile {
     static constexpr int NW = WR * WC, NT = 64 * NW, T = 32 * WR * MR, RB = T / 32;
     static constexpr int S = 4;             // ring slots
-    // Sums in two levels, a chunk of k at a time (see at_pair_kernel), where the
-    // registers hold a second set.
+    // sums in two levels (see at_pair_kernel): where the registers hold a second set
     static constexpr bool TWO = MR * MC <= 4;
-    static constexpr int CHUNK = 32;        // k steps: 512 k
     static constexpr int STAGE = 4 * RB;    // 1 KB blocks per slot: row panel hi, lo, column panel hi, lo
     static constexpr int LPW = STAGE / NW;  // loads per wave per slot
     static_assert(T == 32 * WC * MC && STAGE % NW == 0, "square tiles");
@@ -306,12 +304,13 @@ struct AtTile {
 // nearer to each other than to the rest make it (a bond), the many small products of one
 // sign that come after it fall below half an ulp of the sum and are lost, and the energy,
 // in which the bonds' own terms largely cancel, collects that loss: n = 8192, pairs at
-// 0.3 of the spacing, 7.9e-6 of E against 8.7e-7 by the triplet loop.  Tiles of 128
-// therefore sum 512 k at a time and add those up (7.0e-7; n = 2051 0.350 ms, without
-// 0.346), for which they have the registers.  Tiles of
-// 256 have not: found (given when both sizes are launched) counts sampled rows with such
-// a neighbour, and more than kShortMax of 256 send the call to the smaller tiles (n =
-// 8192 then 15.8 ms instead of 13.9; the loop 52.7).
+// 0.3 / 0.2 of the spacing, 7.9e-6 / 2.2e-5 of E against 8.7e-7 / 2.3e-6 by the triplet
+// loop.  Tiles of 128 therefore sum 512 k at a time and add those up, for which they
+// have the registers (n = 2051 0.350 ms, without 0.346).  Tiles of 256 have not: found
+// (given when both sizes are launched) counts sampled rows with such a neighbour, and
+// more than kShortMax of 256 send the call to the smaller tiles, which then sum 128 k at
+// a time (3.8e-7 / 8.0e-7, with 512 k 7.0e-7 / 2.1e-6; 16.2 and 15.8 ms instead of 13.9,
+// the loop 52.7).
 template <int MAP, int WR, int WC, int MR, int MC, bool GRAD>
 __global__ __launch_bounds__(64 * WR * WC, 2) void at_pair_kernel(
     MapGeom g, int nr, int r0, const uint4 *__restrict__ ops, int KB, int RB, int64_t k0, const float *__restrict__ X,
@@ -373,6 +372,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void at_pair_kernel(
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[m][c][e] = 0.f;
     f32x16_t sum[C::TWO ? MR : 1][C::TWO ? MC : 1];
+    const int chunk = found != nullptr ? 8 : 32;  // k steps
     if constexpr (C::TWO) {
 #pragma unroll
         for (int m = 0; m < MR; ++m)
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void at_pair_kernel(
         step(st, f0, f1);
         step(st + 1, f1, f0);
         if constexpr (C::TWO) {
-            if (st + 2 == nst || (st + 2) % C::CHUNK == 0) {
+            if (st + 2 == nst || ((st + 2) & (chunk - 1)) == 0) {
 #pragma unroll
                 for (int m = 0; m < MR; ++m)
 #pragma unroll

@@ -208,10 +208,9 @@ def triplet_workspace_bytes(n: int, pot: Pot = Pot(), grad: bool = True, stats: 
 
 
 _SIZE_MAX = ctypes.c_size_t(-1).value
-# the sizes the binding asks for at each call: functions of these numbers alone
-_bytes = functools.lru_cache(maxsize=1024)(workspace_bytes)
 
 
+# the sizes the binding asks for at each call: functions of these arguments alone
 @functools.lru_cache(maxsize=1024)
 def _triplet_bytes(n: int, at: bool, grad: bool, stats: bool, limit: int) -> int:
     return triplet_workspace_bytes(n, Pot(at=at), grad, stats, limit)
@@ -229,17 +228,25 @@ def _triplet_ws(n: int, pot: Pot, grad: bool, stats: bool, device) -> torch.Tens
     return _ws(least, device)
 
 
-def _edm_ws(n: int, d: int, prec: int, map, stats: bool, device) -> torch.Tensor | None:
-    """The workspace of a distance call; FP32 can do with the statistics slots, or none."""
-    size, slots = _bytes(1, n, d, prec, map), _bytes(0, 1)
-    if prec == 0:
-        if size > slots:
-            try:
-                return _ws(size, device)
-            except torch.OutOfMemoryError:
-                pass
-        return _ws(slots, device) if stats else None
-    return _ws(size, device)
+@functools.lru_cache(maxsize=1024)
+def _edm_plan(n: int, d: int, prec: str | int, map: str | int, stats: bool):
+    """(prec, map, workspace bytes, the least of them): FP32 can do with the
+    statistics slots, or none."""
+    p, m = PRECS[prec] if isinstance(prec, str) else prec, _map(map)
+    size, slots = workspace_bytes(1, n, d, p, m), workspace_bytes(0, 1)
+    if p != 0:
+        return p, m, size, size
+    least = slots if stats else 0
+    return p, m, size if size > slots else least, least
+
+
+def _edm_ws(size: int, least: int, device) -> torch.Tensor | None:
+    if size > least:
+        try:
+            return _ws(size, device)
+        except torch.OutOfMemoryError:
+            pass
+    return _ws(least, device)
 
 
 # ---------------------------------------------------------------- map dumps
@@ -287,12 +294,13 @@ def edm_packed(X: torch.Tensor, map="lambda", prec="fp32", stats=False, out=None
         raise ValueError("X must be a row-major FP32 matrix")
     n, d = X.shape
     ldx = X.stride(0) if n > 0 else d
-    p = PRECS[prec] if isinstance(prec, str) else int(prec)
+    p, m, size, least = _edm_plan(n, d, prec if isinstance(prec, str) else int(prec),
+                                 map if isinstance(map, str) else int(map), bool(stats))
     D = out if out is not None else torch.empty(n * (n + 1) // 2, dtype=torch.float32, device=X.device)
     s = torch.zeros(4, dtype=torch.int64, device=X.device) if stats else None
-    if ws is None:
-        ws = _edm_ws(n, d, p, map, stats, X.device)
-    _check(lib().smx_edm_packed(_dev(X, "X"), n, d, ldx, _map(map), p, _ptr(D), _ptr(ws),
+    if ws is None and size > 0:
+        ws = _edm_ws(size, least, X.device)
+    _check(lib().smx_edm_packed(_dev(X, "X"), n, d, ldx, m, p, _ptr(D), _ptr(ws),
                                 0 if ws is None else ws.numel(), _ptr(s), _stream()))
     return (D, s) if stats else D
 
@@ -310,14 +318,15 @@ def edm_tiled(X: torch.Tensor, map="lambda", prec="fp32", stats=False, out=None,
         raise ValueError("X must be a row-major FP32 matrix")
     n, d = X.shape
     ldx = X.stride(0) if n > 0 else d
-    p = PRECS[prec] if isinstance(prec, str) else int(prec)
+    p, m, size, least = _edm_plan(n, d, prec if isinstance(prec, str) else int(prec),
+                                 map if isinstance(map, str) else int(map), bool(stats))
     D = out if out is not None else torch.empty(edm_tiled_len(n), dtype=torch.float32, device=X.device)
     if D.dtype != torch.float32 or D.numel() < edm_tiled_len(n) or not D.is_contiguous():
         raise ValueError("out must be a contiguous FP32 tensor of edm_tiled_len(n) elements")
     s = torch.zeros(4, dtype=torch.int64, device=X.device) if stats else None
-    if ws is None:
-        ws = _edm_ws(n, d, p, map, stats, X.device)
-    _check(lib().smx_edm_tiled(_dev(X, "X"), n, d, ldx, _map(map), p, _ptr(D), _ptr(ws),
+    if ws is None and size > 0:
+        ws = _edm_ws(size, least, X.device)
+    _check(lib().smx_edm_tiled(_dev(X, "X"), n, d, ldx, m, p, _ptr(D), _ptr(ws),
                                0 if ws is None else ws.numel(), _ptr(s), _stream()))
     return (D, s) if stats else D
 

@@ -43,7 +43,7 @@ PEAK_FP16 = 2.5e15         # FLOP/s, dense MFMA
 # in profiles/step_matrix_forms_trace_and_traffic.md.  They describe the kernels built
 # from sources with this hash; once those change the figure is reported as null.
 AT_SOURCES = ("smx_triplet_mfma.hip", "smx_at_forms.h", "smx_device.h", "smx_maps.h")
-AT_TRAFFIC = {"src_sha16": "5a51d8b2905f4526", "fetch_bytes": 22.61e9, "write_bytes": 2.75e9}
+AT_TRAFFIC = {"src_sha16": "c498a1f334939173", "fetch_bytes": 24.15e9, "write_bytes": 2.753e9}
 
 N_EDM, D_EDM = 65536, 64
 N_GRAM, D_GRAM = 32768, 512

@@ -178,17 +178,18 @@ static EdmWs edm_ws(int64_t n, int64_t d, int prec) {
         w.inv = off;
         off = align256(off + size_t(n) * 4);
         w.near = off;
-        off = align256(off + 256 * 4);  // kEdmSampleBlocks counts
+        off = align256(off + size_t(kEdmSampleBlocks) * 4);
     }
     w.total = off;
     return w;
 }
 // FP32 on the matrix cores: where the products outweigh the preparation and the
-// wider tiles (a caller may skip the workspace below the first n).  us, matrix /
-// difference form: n = 6000, d = 64 61 / 59, d = 65 66 / 86; n = 8192, d = 36 73 / 109,
-// n = 9001, d = 36 89 / 122, n = 40000, d = 64 1050 / 2430; eight tight
-// clusters (the difference tile in either) n = 9001, d = 37 164 / 143, n = 65536, d = 64
-// 6780 / 6500.
+// wider tiles.  us, matrix / difference form: n = 6000, d = 64 61 / 59, d = 65 66 / 86; n =
+// 8192, d = 36 73 / 109, n = 9001, d = 36 89 / 122, n = 40000, d = 64 1050 / 2430.  (The
+// difference form pays whole chunks of 32 coordinates, the same for d = 33 to 64; below
+// 36 the matrix form's largest element error is the larger one, by up to 30%.)  Tight
+// clusters of any number, the difference tile in either: n = 9001, d = 64 127 / 120, n =
+// 65536, d = 64 6100 / 6250.
 // d <= 8192: the centre lies in LDS.
 static bool edm_fp32_matrix(int64_t n, int64_t d) { return n >= (d > 64 ? 5120 : 8192) && d >= 36 && d <= 8192; }
 

@@ -447,8 +447,9 @@ int launch_edm_gram(const MapGeom &g, int tile, const uint16_t *hi, const uint16
 // FP32 input: one thread a pair where a pass of 64 rows has few, else all of the
 // pass's through LDS.  Its value does not depend on the tile that holds it.  Where more
 // than one of 4096 sampled pairs in 128 is such a pair (kEdmGate), every block takes the
-// difference form's tile.  2-norm error, d = 37 / 64 / 130: 4.5 / 4.8 / 5e-8 against
-// 9.4 / 12 / 17e-8.
+// difference form's tile.  2-norm error, n = 5200 to 8200, normal points, d = 36 / 64 /
+// 130 / 512 / 2000 / 8192: 4.5 / 4.4 / 4.5 / 5.1 / 6.2 / 11e-8 against 9.4 / 12 / 17 / 31 / 60 /
+// 124e-8 (uniform, offset and unevenly scaled points alike).
 //
 // Stores.  Packed rows (i, .) start at any 4-byte offset.  A block's row i is shifted
 // left by s_i < 32 columns to where its piece starts a 128-byte line: rows of tile (X,
@@ -464,15 +465,14 @@ constexpr int kLineLd = kLineCols + 4;   // LDS row: shifted by s_i mod 4 floats
 constexpr int kLineList = 128;
 // share of |x_i|^2 + |x_j|^2 from which a pair's Gram value is kept
 constexpr float kEdmNear = 0.3125f;
-// blocks of the preparation that sample 16 pairs each (edm_ws in smx_abi.hip holds their
-// counts), and the share of near ones, 1 / kEdmGate, above which every block takes the
-// difference tile.  A pass lists up to kLineList pairs, 1.25% of its 10240, and with more
+// kEdmSampleBlocks blocks of the preparation sample 16 pairs each; the share of near ones,
+// 1 / kEdmGate, above which every block takes the difference tile.  A pass lists up to kLineList pairs, 1.25% of its 10240, and with more
 // sums all of them as differences; that many passes overflow, so close to a share of 1%,
 // cost more than the difference tile does.  Never / always that tile, ms, n = 65536, d = 64, tight
 // clusters of equal size in random order: 128 (0.8% near) 3.5 / 6.3, 100 3.7 / 6.3, 90 4.3 /
 // 6.2, 80 7.2 / 6.3, 64 10.7 / 6.3; a single one of a tenth of the points (1%) 5.9 / 6.3; n
 // = 9001, d = 64, the same: 0.115 0.118 0.136 0.183 0.243 and 0.178, against 0.120.
-constexpr int kEdmSampleBlocks = 256, kEdmSamples = kEdmSampleBlocks * 16;
+constexpr int kEdmSamples = kEdmSampleBlocks * 16;
 constexpr unsigned kEdmGate = 128;
 static_assert(kEdmSampleBlocks == 4 * kWave, "four counts a lane");
 

@@ -146,7 +146,8 @@ int launch_edm_diff(const MapGeom &g, int tile, const float *X, int64_t n, int64
                     unsigned long long *slots, bool tiled, hipStream_t s);
 int launch_gram_prep(const float *X, int64_t n, int64_t d, int64_t ldx, int64_t dpad, uint16_t *hi,
                      uint16_t *lo, float *norms, bool split, hipStream_t s);
-// FP32 on the matrix cores (see smx_gram.hip)
+// FP32 on the matrix cores (see smx_gram.hip); near: kEdmSampleBlocks counts
+constexpr int kEdmSampleBlocks = 256;
 int launch_edm_prep(const float *X, int64_t n, int64_t d, int64_t ldx, int64_t dpad, unsigned *near, uint16_t *hi,
                     uint16_t *lo, float *norms, float *inv, hipStream_t s);
 int launch_edm_matrix(const MapGeom &g, const uint16_t *hi, const uint16_t *lo, const float *norms, const float *inv,

@@ -82,56 +82,56 @@ __global__ __launch_bounds__(kQuadWordThreads) void contact_words_kernel(MapGeom
                                                                         uint32_t fill, unsigned long long limit) {
     if (WALK && !quad_dense(cslots, limit)) return;
     for (uint64_t b = launch_index(); !WALK || b < g.G; b += uint64_t(gridDim.x) * gridDim.y) {
-    uint64_t lin;
-    int TX, TY;
-    const bool tile = WALK ? tile2_of_id<MAP>(g, uint32_t(b), lin, TX, TY) : tile2_of<MAP, true>(g, lin, TX, TY);
-    if (!tile) {
-        if (WALK) continue;
-        return;
-    }
-    __shared__ float4 Pc[kQuadTile];
-    const int p = threadIdx.x;
-    const int64_t i = int64_t(TX) * kQuadTile + p, jc = int64_t(TY) * kQuadTile + p;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (jc < n) v = make_float4(Xp[jc * ldx + 0], Xp[jc * ldx + 1], Xp[jc * ldx + 2], 0.f);
-    Pc[p] = v;
-    float xi = 0.f, yi = 0.f, zi = 0.f;
-    if (i < n) {
-        xi = Xp[i * ldx + 0];
-        yi = Xp[i * ldx + 1];
-        zi = Xp[i * ldx + 2];
-    }
-    __syncthreads();
-    uint64_t word = 0;
-    if (i < n) {
-        const int64_t jbase = int64_t(TY) * kQuadTile;
-        const int q0 = TX == TY ? p + 1 : 0;
-        for (int q = q0; q < kQuadTile; ++q) {
-            const float4 c = Pc[q];
-            const float dx = c.x - xi, dy = c.y - yi, dz = c.z - zi;
-            const float s = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
-            if (jbase + q < n && s < rc2) word |= uint64_t(1) << q;
+        uint64_t lin;
+        int TX, TY;
+        const bool tile = WALK ? tile2_of_id<MAP>(g, uint32_t(b), lin, TX, TY) : tile2_of<MAP, true>(g, lin, TX, TY);
+        if (!tile) {
+            if (WALK) continue;
+            return;
         }
-    }
-    if (ROWS) {
-        W[i * g.nb + TY] = word;
-        const unsigned c = items != nullptr ? wave_sum(uint32_t(__builtin_popcountll(word))) : 0;
-        if (c != 0) {
-            int lg = 0;
-            while (lg < kItemLgMax && (c >> lg) > fill) ++lg;
-            const uint32_t parts = 1u << lg, slot = uint32_t(16 * TX + TY) % kSlots;
-            uint32_t at = 0;
-            if (p == 0) at = uint32_t(atomicAdd(cslots + slot * kSlotStride + kSlotItems, (unsigned long long)parts));
-            at = __builtin_amdgcn_readfirstlane(at);
-            for (uint32_t e = p; e < parts; e += kQuadTile)
-                if (at + e < cap) items[slot * cap + at + e] = item_pack(TX, TY, int(e), lg);
-            if (p == 0 && at + parts > cap) atomicOr(cslots + kSlotFull, 1ull);
+        __shared__ float4 Pc[kQuadTile];
+        const int p = threadIdx.x;
+        const int64_t i = int64_t(TX) * kQuadTile + p, jc = int64_t(TY) * kQuadTile + p;
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (jc < n) v = make_float4(Xp[jc * ldx + 0], Xp[jc * ldx + 1], Xp[jc * ldx + 2], 0.f);
+        Pc[p] = v;
+        float xi = 0.f, yi = 0.f, zi = 0.f;
+        if (i < n) {
+            xi = Xp[i * ldx + 0];
+            yi = Xp[i * ldx + 1];
+            zi = Xp[i * ldx + 2];
         }
-    } else {
-        W[int64_t(TY) * npad + i] = word;
-    }
-    if (!WALK) return;
-    __syncthreads();  // Pc is free for the next tile
+        __syncthreads();
+        uint64_t word = 0;
+        if (i < n) {
+            const int64_t jbase = int64_t(TY) * kQuadTile;
+            const int q0 = TX == TY ? p + 1 : 0;
+            for (int q = q0; q < kQuadTile; ++q) {
+                const float4 c = Pc[q];
+                const float dx = c.x - xi, dy = c.y - yi, dz = c.z - zi;
+                const float s = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
+                if (jbase + q < n && s < rc2) word |= uint64_t(1) << q;
+            }
+        }
+        if (ROWS) {
+            W[i * g.nb + TY] = word;
+            const unsigned c = items != nullptr ? wave_sum(uint32_t(__builtin_popcountll(word))) : 0;
+            if (c != 0) {
+                int lg = 0;
+                while (lg < kItemLgMax && (c >> lg) > fill) ++lg;
+                const uint32_t parts = 1u << lg, slot = uint32_t(16 * TX + TY) % kSlots;
+                uint32_t at = 0;
+                if (p == 0) at = uint32_t(atomicAdd(cslots + slot * kSlotStride + kSlotItems, (unsigned long long)parts));
+                at = __builtin_amdgcn_readfirstlane(at);
+                for (uint32_t e = p; e < parts; e += kQuadTile)
+                    if (at + e < cap) items[slot * cap + at + e] = item_pack(TX, TY, int(e), lg);
+                if (p == 0 && at + parts > cap) atomicOr(cslots + kSlotFull, 1ull);
+            }
+        } else {
+            W[int64_t(TY) * npad + i] = word;
+        }
+        if (!WALK) return;
+        __syncthreads();  // Pc is free for the next tile
     }
 }
 
@@ -207,70 +207,70 @@ __global__ __launch_bounds__(kQuadThreads) void clique_rows_kernel(int nb, const
     };
     unsigned long long cnt = 0;
     for (uint32_t e = q0; e < len; e += step) {
-    int X, Y, part, lg;
-    if (LISTED) {
-        const uint32_t item = __builtin_amdgcn_readfirstlane(items[slot * cap + e]);
-        X = int(item & 255u), Y = int(item >> 8 & 255u), part = int(item >> 16 & 255u), lg = int(item >> 24);
-    } else {
-        linear2(wv >> 6, X, Y);
-        if (Y >= nb) return;
-        part = int(wv & 63u), lg = 6;
-    }
-    const int64_t i0 = int64_t(X) * kQuadTile;
-    const int lgrow = lg < 6 ? lg : 6, lgcol = lg - lgrow;
-    const bool mine = (lane & ((1 << lgrow) - 1)) == (part & ((1 << lgrow) - 1));
-    const uint64_t cols = (lgcol == 0 ? ~0ull : lgcol == 1 ? 0x5555555555555555ull : 0x1111111111111111ull) << (part >> lgrow);
-    const uint64_t word = mine ? R[(i0 + lane) * nb + Y] & cols : 0;
-    uint64_t act = __ballot(word != 0);
-    while (act != 0) {
-        const int p = __builtin_ctzll(act);
-        act &= act - 1;
-        uint64_t mi[NQ];
+        int X, Y, part, lg;
+        if (LISTED) {
+            const uint32_t item = __builtin_amdgcn_readfirstlane(items[slot * cap + e]);
+            X = int(item & 255u), Y = int(item >> 8 & 255u), part = int(item >> 16 & 255u), lg = int(item >> 24);
+        } else {
+            linear2(wv >> 6, X, Y);
+            if (Y >= nb) return;
+            part = int(wv & 63u), lg = 6;
+        }
+        const int64_t i0 = int64_t(X) * kQuadTile;
+        const int lgrow = lg < 6 ? lg : 6, lgcol = lg - lgrow;
+        const bool mine = (lane & ((1 << lgrow) - 1)) == (part & ((1 << lgrow) - 1));
+        const uint64_t cols = (lgcol == 0 ? ~0ull : lgcol == 1 ? 0x5555555555555555ull : 0x1111111111111111ull) << (part >> lgrow);
+        const uint64_t word = mine ? R[(i0 + lane) * nb + Y] & cols : 0;
+        uint64_t act = __ballot(word != 0);
+        while (act != 0) {
+            const int p = __builtin_ctzll(act);
+            act &= act - 1;
+            uint64_t mi[NQ];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) mi[q] = row(i0 + p, Y, q);
-        uint64_t js = lane64(word, p);
-        while (js != 0) {
-            const int64_t j = int64_t(Y) * kQuadTile + __builtin_ctzll(js);
-            js &= js - 1;
-            uint64_t m[NQ];
+            for (int q = 0; q < NQ; ++q) mi[q] = row(i0 + p, Y, q);
+            uint64_t js = lane64(word, p);
+            while (js != 0) {
+                const int64_t j = int64_t(Y) * kQuadTile + __builtin_ctzll(js);
+                js &= js - 1;
+                uint64_t m[NQ];
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) m[q] = mi[q] & row(j, Y, q);
+                for (int q = 0; q < NQ; ++q) m[q] = mi[q] & row(j, Y, q);
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                uint64_t nz = __ballot(m[q] != 0);
-                int wl = 0;
-                uint64_t ks = 0;
-                while (ks != 0 || nz != 0) {
-                    int64_t k[4];
-                    int have = 0;
+                for (int q = 0; q < NQ; ++q) {
+                    uint64_t nz = __ballot(m[q] != 0);
+                    int wl = 0;
+                    uint64_t ks = 0;
+                    while (ks != 0 || nz != 0) {
+                        int64_t k[4];
+                        int have = 0;
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        if (ks == 0 && nz != 0) {
-                            wl = __builtin_ctzll(nz);
-                            nz &= nz - 1;
-                            ks = lane64(m[q], wl);
+                        for (int u = 0; u < 4; ++u) {
+                            if (ks == 0 && nz != 0) {
+                                wl = __builtin_ctzll(nz);
+                                nz &= nz - 1;
+                                ks = lane64(m[q], wl);
+                            }
+                            k[u] = -1;
+                            if (ks != 0) {
+                                k[u] = int64_t(wl + 64 * q) * kQuadTile + __builtin_ctzll(ks);
+                                ks &= ks - 1;
+                                ++have;
+                            }
                         }
-                        k[u] = -1;
-                        if (ks != 0) {
-                            k[u] = int64_t(wl + 64 * q) * kQuadTile + __builtin_ctzll(ks);
-                            ks &= ks - 1;
-                            ++have;
-                        }
+                        uint64_t r[4][NQ];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+#pragma unroll
+                            for (int v = q; v < NQ; ++v)
+                                r[u][v] = u < have && m[v] != 0 ? row(k[u], int(k[u] >> 6), v) : 0;
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+#pragma unroll
+                            for (int v = q; v < NQ; ++v) cnt += unsigned(__builtin_popcountll(m[v] & r[u][v]));
                     }
-                    uint64_t r[4][NQ];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-#pragma unroll
-                        for (int v = q; v < NQ; ++v)
-                            r[u][v] = u < have && m[v] != 0 ? row(k[u], int(k[u] >> 6), v) : 0;
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-#pragma unroll
-                        for (int v = q; v < NQ; ++v) cnt += unsigned(__builtin_popcountll(m[v] & r[u][v]));
                 }
             }
         }
-    }
     }
     const unsigned long long c = wave_sum(cnt);
     if (lane == 0 && c != 0) atomicAdd(cslots + slot * kSlotStride, c);
@@ -324,91 +324,91 @@ __global__ __launch_bounds__(kQuadThreads) void quad_kernel(MapGeom g, const uin
         return;
     }
     for (bool more_ids = true; more_ids;) {
-    uint64_t chunk = wave, end = wave + 1;
-    if (walk) {
-        uint32_t k = 0;
-        if (p == 0) k = uint32_t(atomicAdd(cslots + (wave % kSlots) * kSlotStride + kSlotWalk, 1ull));
-        chunk = (uint64_t(__builtin_amdgcn_readfirstlane(k)) * kSlots + wave % kSlots) * grab;
-        end = chunk + grab;
-    }
-    more_ids = walk && end * kWave < g.G;
-    for (; chunk < end && chunk * kWave < g.G; ++chunk) {
-    const uint64_t base = chunk * kWave;
-
-    uint64_t mylin = 0;
-    int Tq[4] = {0, 0, 0, 0};
-    bool ok = false;
-    if (base + uint64_t(p) < g.G) ok = tile4_of_id<MAP>(g, uint32_t(base + uint64_t(p)), mylin, Tq);
-    uint64_t mask = __ballot(ok);
-
-    // coordinates of the tile decoded by lane q (q uniform), and its words
-    auto coords = [&](int q, int T[4]) {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) T[d] = __builtin_amdgcn_readlane(Tq[d], q);
-    };
-    auto load = [&](const int T[4], uint64_t a[6]) {
-#pragma unroll
-        for (int s = 0; s < 6; ++s) {
-            const int64_t ra = s < 3 ? T[0] : (s < 5 ? T[1] : T[2]);
-            const int64_t cb = s == 0 ? T[1] : (s == 1 || s == 3) ? T[2] : T[3];
-            a[s] = W[cb * npad + ra * kQuadTile + p];
+        uint64_t chunk = wave, end = wave + 1;
+        if (walk) {
+            uint32_t k = 0;
+            if (p == 0) k = uint32_t(atomicAdd(cslots + (wave % kSlots) * kSlotStride + kSlotWalk, 1ull));
+            chunk = (uint64_t(__builtin_amdgcn_readfirstlane(k)) * kSlots + wave % kSlots) * grab;
+            end = chunk + grab;
         }
-    };
+        more_ids = walk && end * kWave < g.G;
+        for (; chunk < end && chunk * kWave < g.G; ++chunk) {
+            const uint64_t base = chunk * kWave;
 
-    uint32_t cnt = 0;
-    if (mask != 0) {
-        int q = __builtin_ctzll(mask);
-        mask &= mask - 1;
-        int T[4];
-        uint64_t a[6];
-        coords(q, T);
-        load(T, a);
-        while (true) {
-            const bool more = mask != 0;
-            int qn = 0, Tn[4] = {0, 0, 0, 0};
-            uint64_t an[6] = {0, 0, 0, 0, 0, 0};
-            if (more) {
-                qn = __builtin_ctzll(mask);
-                mask &= mask - 1;
-                coords(qn, Tn);
-                load(Tn, an);
-            }
-            // the previous tile's reads of this wave's LDS are done before it is
-            // overwritten, and the writes land before other lanes read them
-            __builtin_amdgcn_wave_barrier();
+            uint64_t mylin = 0;
+            int Tq[4] = {0, 0, 0, 0};
+            bool ok = false;
+            if (base + uint64_t(p) < g.G) ok = tile4_of_id<MAP>(g, uint32_t(base + uint64_t(p)), mylin, Tq);
+            uint64_t mask = __ballot(ok);
+
+            // coordinates of the tile decoded by lane q (q uniform), and its words
+            auto coords = [&](int q, int T[4]) {
 #pragma unroll
-            for (int s = 0; s < 3; ++s) Aw[s][p] = a[3 + s];
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            uint64_t bits = a[0];
-            while (bits != 0) {
-                const int p2 = __builtin_ctzll(bits);
-                bits &= bits - 1;
-                uint64_t m3 = a[1] & Aw[0][p2];
-                const uint64_t wv = a[2] & Aw[1][p2];
-                while (m3 != 0) {
-                    const int p3 = __builtin_ctzll(m3);
-                    m3 &= m3 - 1;
-                    cnt += uint32_t(__builtin_popcountll(wv & Aw[2][p3]));
+                for (int d = 0; d < 4; ++d) T[d] = __builtin_amdgcn_readlane(Tq[d], q);
+            };
+            auto load = [&](const int T[4], uint64_t a[6]) {
+#pragma unroll
+                for (int s = 0; s < 6; ++s) {
+                    const int64_t ra = s < 3 ? T[0] : (s < 5 ? T[1] : T[2]);
+                    const int64_t cb = s == 0 ? T[1] : (s == 1 || s == 3) ? T[2] : T[3];
+                    a[s] = W[cb * npad + ra * kQuadTile + p];
+                }
+            };
+
+            uint32_t cnt = 0;
+            if (mask != 0) {
+                int q = __builtin_ctzll(mask);
+                mask &= mask - 1;
+                int T[4];
+                uint64_t a[6];
+                coords(q, T);
+                load(T, a);
+                while (true) {
+                    const bool more = mask != 0;
+                    int qn = 0, Tn[4] = {0, 0, 0, 0};
+                    uint64_t an[6] = {0, 0, 0, 0, 0, 0};
+                    if (more) {
+                        qn = __builtin_ctzll(mask);
+                        mask &= mask - 1;
+                        coords(qn, Tn);
+                        load(Tn, an);
+                    }
+                    // the previous tile's reads of this wave's LDS are done before it is
+                    // overwritten, and the writes land before other lanes read them
+                    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                    for (int s = 0; s < 3; ++s) Aw[s][p] = a[3 + s];
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    uint64_t bits = a[0];
+                    while (bits != 0) {
+                        const int p2 = __builtin_ctzll(bits);
+                        bits &= bits - 1;
+                        uint64_t m3 = a[1] & Aw[0][p2];
+                        const uint64_t wv = a[2] & Aw[1][p2];
+                        while (m3 != 0) {
+                            const int p3 = __builtin_ctzll(m3);
+                            m3 &= m3 - 1;
+                            cnt += uint32_t(__builtin_popcountll(wv & Aw[2][p3]));
+                        }
+                    }
+                    if (STATS && p == 0) {
+                        const uint64_t lin = uint64_t(__builtin_amdgcn_readlane(uint32_t(mylin), q)) |
+                                             (uint64_t(__builtin_amdgcn_readlane(uint32_t(mylin >> 32), q)) << 32);
+                        stats_add(sslots, lin, quad_tile_volume(T, n), 0);
+                    }
+                    if (!more) break;
+                    q = qn;
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) T[d] = Tn[d];
+#pragma unroll
+                    for (int s = 0; s < 6; ++s) a[s] = an[s];
                 }
             }
-            if (STATS && p == 0) {
-                const uint64_t lin = uint64_t(__builtin_amdgcn_readlane(uint32_t(mylin), q)) |
-                                     (uint64_t(__builtin_amdgcn_readlane(uint32_t(mylin >> 32), q)) << 32);
-                stats_add(sslots, lin, quad_tile_volume(T, n), 0);
-            }
-            if (!more) break;
-            q = qn;
-#pragma unroll
-            for (int d = 0; d < 4; ++d) T[d] = Tn[d];
-#pragma unroll
-            for (int s = 0; s < 6; ++s) a[s] = an[s];
+            const unsigned c = wave_sum(cnt);
+            if (p == 0 && c != 0) atomicAdd(cslots + (base / kWave % kSlots) * kSlotStride, (unsigned long long)c);
         }
-    }
-    const unsigned c = wave_sum(cnt);
-    if (p == 0 && c != 0) atomicAdd(cslots + (base / kWave % kSlots) * kSlotStride, (unsigned long long)c);
-    }
     }
     if (walk && last_block(cslots + kSlotDone)) write_count(cslots, out);
 }
